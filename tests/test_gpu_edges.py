@@ -1,0 +1,91 @@
+"""GPU parity of the kernels at the edges of their tiles: remainders, the
+smallest sizes of each variant and the sizes on either side of a dispatch line."""
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2605_06892_amd import hsa_step as H
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda"
+
+
+def _gen(seed):
+    return torch.Generator(device="cpu").manual_seed(seed)
+
+
+def _attend64(q, k, v, heads):
+    n, d = q.shape
+    dh = d // heads
+    o = torch.empty(n, d, dtype=torch.float64)
+    for h in range(heads):
+        c = slice(h * dh, (h + 1) * dh)
+        s = torch.softmax(q[:, c].double() @ k[:, c].double().t() * dh ** -0.5, dim=1)
+        o[:, c] = s @ v[:, c].double()
+    return o
+
+
+# queries around the 16- and 32-query workgroups, rows around the 32-key blocks and the 8 waves'
+# share of 256; (80, 16 heads) launches 32-query workgroups on 256 compute units, the others 16
+@pytest.mark.parametrize("n_q,n_kv,heads,dh", [
+    (1, 1, 1, 64), (15, 31, 2, 64), (16, 32, 1, 128), (17, 33, 2, 128), (31, 255, 3, 64), (33, 257, 2, 64),
+    (33, 289, 2, 128), (300, 77, 16, 64), (300, 290, 16, 128), (289, 512, 16, 64),
+])
+@pytest.mark.parametrize("spread", [1.0, 30.0])
+def test_attention_f32_edges(n_q, n_kv, heads, dh, spread):
+    """spread 30: scores hundreds apart, so most probabilities underflow."""
+    g = _gen(n_q * 1000 + n_kv)
+    d = heads * dh
+    q, k, v = (torch.randn(n, d, generator=g) for n in (n_q, n_kv, n_kv))
+    q *= spread
+    out = torch.full((n_q + 1, d), 7.0, device=DEV)
+    H.hsa_attention_core(q.to(DEV), k.to(DEV), v.to(DEV), n_q, heads, dh, dh ** -0.5, out)
+    want = _attend64(q, k, v, heads)
+    # a score of magnitude s carries an error of about dh/2 ulps of s / sqrt(dh) at most, which is
+    # the relative error of its probability; the sums add a few ulps
+    bar = 2.0 ** -24 * (64 + 8 * spread * dh ** 0.5)
+    assert float((out[:n_q].cpu().double() - want).abs().max() / want.abs().max()) < bar
+    assert torch.all(out[n_q] == 7.0)
+
+
+def test_attention_f32_infinite_and_nan_scores():
+    """A -inf score has probability 0, a NaN score makes its own row NaN and no other."""
+    g = _gen(5)
+    q, k, v = torch.rand(3, 64, generator=g) + 0.5, torch.randn(300, 64, generator=g), torch.randn(300, 64, generator=g)
+    k[40:100] = -float("inf")  # whole blocks of one wave's share among them
+    q[1, 3] = float("nan")
+    out = torch.empty(3, 64, device=DEV)
+    H.hsa_attention_core(q.to(DEV), k.to(DEV), v.to(DEV), 3, 1, 64, 0.125, out)
+    keep = torch.cat([torch.arange(40), torch.arange(100, 300)])
+    want = _attend64(q[[0, 2]], k[keep], v[keep], 1)
+    got = out.cpu()
+    assert float((got[[0, 2]].double() - want).abs().max()) < 1e-5
+    assert torch.isnan(got[1]).all()
+
+
+# rows and columns around the 32 and 64 tiles, k around the 4-float loads and the slabs; 300 x 96 x 3
+# outputs take the split-k tiles, 1500 x 1100 the 64 x 64 tiles on 256 compute units
+@pytest.mark.parametrize("m,n,k", [(1, 1, 1), (31, 33, 3), (33, 31, 63), (65, 64, 64), (300, 96, 65), (1500, 1100, 37),
+                                   (1537, 1025, 96)])
+@pytest.mark.parametrize("option", ["plain", "scale_gelu", "residual"])
+def test_linear_f32_edges(m, n, k, option):
+    g = _gen(m + n + k)
+    x, w, r = torch.randn(m, k, generator=g), torch.randn(n, k, generator=g), torch.randn(m, n, generator=g)
+    s = torch.rand(m, generator=g) + 0.5
+    y = torch.full((m + 1, n), 7.0, device=DEV)
+    want = x.double() @ w.double().t()
+    kw = {}
+    if option == "scale_gelu":
+        kw = {"row_scale": s.to(DEV), "gelu": True}
+        z = want * s.double()[:, None]
+        want = 0.5 * z * (1 + torch.tanh(np.sqrt(2 / np.pi) * (z + 0.044715 * z ** 3)))
+    elif option == "residual":
+        kw = {"residual": r.to(DEV)}
+        want = want + r.double()
+    H.hsa_linear(x.to(DEV), m, w.to(DEV), y, **kw)
+    # k sums of products of size sqrt(k) ulps each, a few ulps for the epilogue
+    bar = 2.0 ** -24 * (16 + 4 * k ** 0.5) * max(1.0, float(want.abs().max()))
+    assert float((y[:m].cpu().double() - want).abs().max()) < bar
+    assert torch.all(y[m] == 7.0)
