@@ -3,7 +3,7 @@
 //   * gather_latent: the fp32 latent rows of the active tokens, converted to
 //     the model dtype, as the compact input of the patch embedding (Section
 //     2.3: only the active rows flow through the model).
-//   * velocity_keys + rank_budgets: the group refresh. Group sizes are fixed
+//   * velocity_keys + select_budgets: the group refresh. Group sizes are fixed
 //     and membership follows a per-token velocity ranking (Section 2.2,
 //     Appendix B): the key of a token is the squared L2 norm of its velocity,
 //     a float64 sum of the exact squares in channel order, and its rank is
@@ -26,8 +26,8 @@
 //     normalized rows are never written: the GEMM epilogue scales its rows.
 //
 // All of them are small (N x C fp32 reads, N budgets, one read of the hidden
-// state): one pass each, grid-stride loops; the ranking compares every pair of
-// keys from LDS tiles, O(N^2) VALU work that runs once per refresh.
+// state): one pass each, grid-stride loops; the ranking needs only the group
+// boundaries, which one workgroup finds by histogram.
 #include "common.h"
 
 namespace hsa {
@@ -162,42 +162,302 @@ __global__ __launch_bounds__(kThreads) void velocity_keys_scalar(const float* __
   }
 }
 
-// 64 tokens per workgroup (one per lane); the four waves split each LDS tile
-// of keys and their counts are summed at the end.
-constexpr int kRankTokens = 64, kRankTile = 1024;
+// Group assignment by selection. A token's group is the number of group
+// boundaries (ranks end[0], end[1], ...) at or below its rank, so only the
+// neighbourhoods of the at most 15 boundaries need ranks. One workgroup:
+//   1. minimum and maximum key;
+//   2. a histogram of the keys over kSelBins equal ranges of bit patterns from
+//      minimum to maximum (LDS atomics), scanned: a bin with no boundary inside
+//      has one group, whose budget replaces its count;
+//   3. every token reads its bin's budget; the keys of the bins with a boundary
+//      inside, a few dozen, are collected and ranked by comparing all pairs.
+// A bin too full for that (an outlier that widens the range, or many equal
+// keys) is divided again around each of its boundaries, first by key, then,
+// among equal keys, by token index, until the boundary's element (key, token)
+// is found; its keys are then compared with those elements.
+// Steps 1 and 2 and the lookup of 3 use the upper halves of the keys (sign,
+// exponent and 20 mantissa bits), which stay in registers for up to 81920
+// tokens; whole keys are read again for the collected ones only. The bound is
+// one CU's loads, LDS atomics and instruction fetches; spreading the steps over
+// CUs needs scratch memory and more launches, at 3 us each, than it saves.
+// Comparing all pairs of keys on the whole chip took 303 us at 32760 tokens and
+// 1125 us at 75600, this takes 17 and 42 us (26 and 59 with whole keys in
+// registers, or read from L2 by every step).
+constexpr int kSelThreads = 1024, kSelBinBits = 13, kSelBins = 1 << kSelBinBits;
+constexpr int kSelList = 1024;     // collected keys
+constexpr int kSelBig = -64;       // histogram code of a bin too full for the list
+// KEYS: upper halves per thread in registers (0: read by each step)
+template <int KEYS>
+__global__ __launch_bounds__(kSelThreads) void select_budgets(const unsigned long long* __restrict__ keys,
+                                                              int n, GroupTable tab,
+                                                              int32_t* __restrict__ budget) {
+  typedef unsigned long long u64;
+  constexpr int kWaves = kSelThreads / kWave, kPer = kSelBins / kSelThreads;
+  constexpr unsigned kNone = 0xFFFFFFFFu;  // no token: above every key's upper half
+  __shared__ __attribute__((aligned(16))) int hist[kSelBins + 4];  // and a bin for no token
+  __shared__ u64 list_key[kSelList];
+  __shared__ int list_tok[kSelList];
+  __shared__ unsigned red_lo[kWaves], red_hi[kWaves];
+  __shared__ int wave_total[kWaves];
+  __shared__ int end_at[kMaxGroups], budget_of[kMaxGroups];
+  __shared__ int bin_of[kMaxGroups], before_of[kMaxGroups], count_of[kMaxGroups], slot_of[kMaxGroups];
+  __shared__ int slot_off[kMaxGroups + 1], slot_fill[kMaxGroups], slot_before[kMaxGroups], n_slots, n_big;
+  __shared__ int sub_bin, sub_before, sub_count;
+  __shared__ u64 thr_key[kMaxGroups];
+  __shared__ int thr_tok[kMaxGroups];
+  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+  const int nb = tab.n - 1;  // boundaries
 
-__global__ __launch_bounds__(kThreads) void rank_budgets(const unsigned long long* __restrict__ keys,
-                                                         int n, GroupTable tab,
-                                                         int32_t* __restrict__ budget) {
-  __shared__ unsigned long long tile[kRankTile];
-  __shared__ int partial[kThreads / kWave][kRankTokens];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int t = blockIdx.x * kRankTokens + lane;
-  const unsigned long long kt = t < n ? key_bits(keys[t]) : 0ull;
-  int count = 0;
-  for (int m0 = 0; m0 < n; m0 += kRankTile) {
-    const int cnt = min(kRankTile, n - m0);
-    __syncthreads();  // the previous tile is no longer read
-    for (int e = threadIdx.x; e < cnt; e += kThreads) tile[e] = key_bits(keys[m0 + e]);
+  // upper half of the key of token t as it is stored, and of its key_bits
+  auto load = [&](long t) -> unsigned { return reinterpret_cast<const unsigned*>(keys)[2 * min(t, (long)n - 1) + 1]; };
+  auto top_bits = [&](unsigned hi, long t) -> unsigned {
+    if (t >= n) return kNone;
+    if ((hi & 0x7FF00000u) == 0x7FF00000u) return (unsigned)(key_bits(keys[t]) >> 32);  // infinite or NaN
+    return hi;
+  };
+  unsigned top[KEYS > 0 ? KEYS : 1];
+  if constexpr (KEYS > 0) {
+    // buffer loads: one lane offset and a scalar step, no address per load
+    const auto rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<u64*>(keys), 0, n * 8, 0x00020000);
+#pragma unroll
+    for (int i = 0; i < KEYS; ++i) {
+      top[i] = kNone;
+      if (i * kSelThreads + tid < n)
+        top[i] = __builtin_amdgcn_raw_buffer_load_b32(rs, tid * 8 + 4, i * kSelThreads * 8, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < KEYS; ++i) top[i] = top_bits(top[i], i * kSelThreads + tid);
+  }
+  // f(upper half, token) for every key of this thread
+  auto each = [&](auto&& f) __attribute__((always_inline)) {
+    if constexpr (KEYS > 0) {
+#pragma unroll
+      for (int i = 0; i < KEYS; ++i) f(top[i], (long)i * kSelThreads + tid);
+    } else {
+      constexpr int V = 16;
+#pragma unroll 1
+      for (long t0 = tid; t0 < n; t0 += (long)V * kSelThreads) {
+        unsigned k[V];
+#pragma unroll
+        for (int i = 0; i < V; ++i) k[i] = load(t0 + (long)i * kSelThreads);
+#pragma unroll
+        for (int i = 0; i < V; ++i) f(top_bits(k[i], t0 + (long)i * kSelThreads), t0 + (long)i * kSelThreads);
+      }
+    }
+  };
+  // f(key bits, token), for the steps that only the division of full bins takes
+  auto each_again = [&](auto&& f) __attribute__((always_inline)) {
+#pragma unroll 1
+    for (long t = tid; t < n; t += kSelThreads) f(key_bits(keys[t]), (int)t);
+  };
+  auto clear_hist = [&]() {
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) hist[i * kSelThreads + tid] = 0;
     __syncthreads();
-    const int lo = wave * (kRankTile / 4);
-    const int hi = min(lo + kRankTile / 4, cnt);
-#pragma unroll 8
-    for (int e = lo; e < hi; ++e) {
-      const unsigned long long km = tile[e];
-      count += (km < kt) | ((km == kt) & (m0 + e < t));
+  };
+  // Counts of this thread's kPer bins, and the keys before the first of them.
+  auto scan_bins = [&](int (&c)[kPer]) -> int {
+    __syncthreads();
+    int sum = 0;
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+      c[i] = hist[tid * kPer + i];
+      sum += c[i];
+    }
+    int inc = sum;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+      const int y = __shfl_up(inc, o);
+      if (lane >= o) inc += y;
+    }
+    if (lane == kWave - 1) wave_total[wave] = inc;
+    __syncthreads();
+    int p = inc - sum;
+    for (int w = 0; w < wave; ++w) p += wave_total[w];
+    return p;
+  };
+  // rank of list element i within the list elements a .. b-1
+  auto rank_in = [&](int i, int a, int b) -> int {
+    const u64 k = list_key[i];
+    const int t = list_tok[i];
+    int r = 0;
+    for (int j = a; j < b; ++j) r += (list_key[j] < k) | ((list_key[j] == k) & (list_tok[j] < t));
+    return r;
+  };
+
+  if (tid < kMaxGroups) {
+    end_at[tid] = tid < nb ? (int)tab.end[tid] : 0;
+    budget_of[tid] = tid <= nb ? tab.budget[tid] : 0;
+    bin_of[tid] = -1;  // no bin has this boundary inside
+    slot_fill[tid] = 0;
+  }
+  unsigned lo32 = kNone, hi32 = 0;  // hi32: one above the maximum
+  each([&](unsigned k, long) {
+    lo32 = min(lo32, k);
+    hi32 = max(hi32, k + 1);
+  });
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    lo32 = min(lo32, (unsigned)__shfl_xor((int)lo32, o));
+    hi32 = max(hi32, (unsigned)__shfl_xor((int)hi32, o));
+  }
+  if (lane == 0) {
+    red_lo[wave] = lo32;
+    red_hi[wave] = hi32;
+  }
+  clear_hist();
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) {
+    lo32 = min(lo32, red_lo[w]);
+    hi32 = max(hi32, red_hi[w]);
+  }
+  const int bits = hi32 - 1 > lo32 ? 32 - __clz(hi32 - 1 - lo32) : 0;
+  const int shift32 = bits > kSelBinBits ? bits - kSelBinBits : 0;
+  const u64 lo = (u64)lo32 << 32;  // the bins in whole keys
+  const int shift = shift32 + 32;
+  auto bin32 = [&](unsigned k) { return k == kNone ? kSelBins : (int)((k - lo32) >> shift32); };
+  each([&](unsigned k, long) { atomicAdd(&hist[bin32(k)], 1); });
+
+  {
+    int c[kPer];
+    int p = scan_bins(c), sum = 0, g0 = 0, g1 = 0;
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) sum += c[i];
+    for (int g = 0; g < nb; ++g) {  // ascending: g0 at or below p, g1 below the end of this thread's bins
+      const int e = end_at[g];
+      g0 += e <= p;
+      g1 += e <= p || e - p < sum;
+    }
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) hist[tid * kPer + i] = budget_of[g0];
+    if (g0 < g1) {
+#pragma unroll
+      for (int i = 0; i < kPer; ++i) {
+        while (g0 < g1 && end_at[g0] <= p) ++g0;
+        hist[tid * kPer + i] = budget_of[g0];
+        for (int g = g0; g < g1 && end_at[g] - p < c[i]; ++g) {  // inside: keys of this bin on both sides
+          bin_of[g] = tid * kPer + i;
+          before_of[g] = p;
+          count_of[g] = c[i];
+        }
+        p += c[i];
+      }
     }
   }
-  partial[wave][lane] = count;
   __syncthreads();
-  if (wave == 0 && t < n) {
-    int r = 0;
-#pragma unroll
-    for (int w = 0; w < kThreads / kWave; ++w) r += partial[w][lane];
-    int g = 0;
-    while (g + 1 < tab.n && r >= tab.end[g]) ++g;
-    budget[t] = tab.budget[g];
+  if (tid == 0) {  // a slot of the list for every bin with a boundary inside
+    int slots = 0, fill = 0, last = -1, big = 0;
+    for (int g = 0; g < nb; ++g) {  // ascending ranks: equal bins are adjacent
+      slot_of[g] = -1;
+      if (bin_of[g] < 0) continue;
+      if (last >= 0 && bin_of[last] == bin_of[g]) {
+        slot_of[g] = slot_of[last];
+      } else if (count_of[g] <= kSelList - fill) {
+        slot_off[slots] = fill;
+        slot_before[slots] = before_of[g];
+        fill += count_of[g];
+        hist[bin_of[g]] = -1 - slots;
+        slot_of[g] = slots++;
+      } else {
+        hist[bin_of[g]] = kSelBig;
+        big = 1;
+      }
+      last = g;
+    }
+    slot_off[slots] = fill;
+    n_slots = slots;
+    n_big = big;
   }
+  __syncthreads();
+  each([&](unsigned k, long t) {
+    const int code = hist[bin32(k)];
+    if (t >= n) return;
+    if (code >= 0) {
+      budget[t] = code;
+    } else if (code != kSelBig) {
+      const int at = slot_off[-1 - code] + atomicAdd(&slot_fill[-1 - code], 1);
+      list_tok[at] = (int)t;
+    }
+  });
+  __syncthreads();
+  const int listed = slot_off[n_slots];
+  for (int i = tid; i < listed; i += kSelThreads) list_key[i] = key_bits(keys[list_tok[i]]);
+  __syncthreads();
+  for (int i = tid; i < listed; i += kSelThreads) {
+    int s = 0;
+    while (i >= slot_off[s + 1]) ++s;
+    const int r = slot_before[s] + rank_in(i, slot_off[s], slot_off[s + 1]);
+    int group = 0;
+    for (int g = 0; g < nb; ++g) group += end_at[g] <= r;
+    budget[list_tok[i]] = budget_of[group];
+  }
+  if (!n_big) return;
+
+  for (int g = 0; g < nb; ++g) {  // the element of each boundary inside a bin that did not fit
+    if (bin_of[g] < 0 || slot_of[g] >= 0) continue;
+    const int e = end_at[g];
+    u64 k0 = lo + ((u64)bin_of[g] << shift);
+    int ks = shift, t0 = 0, ts = 32 - __clz(n);  // keys k0 .. k0 + 2^ks - 1, tokens t0 .. t0 + 2^ts - 1
+    int before = before_of[g], count = count_of[g];
+    while (count > kSelList) {
+      const bool by_key = ks > 0;
+      const int bits_left = by_key ? ks : ts, sh = bits_left > kSelBinBits ? bits_left - kSelBinBits : 0;
+      clear_hist();
+      each_again([&](u64 k, int t) {
+        if (k >= k0 && (k - k0) >> ks == 0 && t >= t0 && (t - t0) >> ts == 0)
+          atomicAdd(&hist[by_key ? (int)((k - k0) >> sh) : (t - t0) >> sh], 1);
+      });
+      int c[kPer];
+      int p = before + scan_bins(c);
+#pragma unroll
+      for (int i = 0; i < kPer; ++i) {
+        if (e >= p && e - p < c[i]) {
+          sub_bin = tid * kPer + i;
+          sub_before = p;
+          sub_count = c[i];
+        }
+        p += c[i];
+      }
+      __syncthreads();
+      if (by_key) {
+        k0 += (u64)sub_bin << sh;
+        ks = sh;
+      } else {
+        t0 += sub_bin << sh;
+        ts = sh;
+      }
+      before = sub_before;
+      count = sub_count;
+    }
+    __syncthreads();  // the list is no longer read
+    if (tid == 0) slot_fill[0] = 0;
+    __syncthreads();
+    each_again([&](u64 k, int t) {
+      if (k >= k0 && (k - k0) >> ks == 0 && t >= t0 && (t - t0) >> ts == 0) {
+        const int at = atomicAdd(&slot_fill[0], 1);
+        list_key[at] = k;
+        list_tok[at] = t;
+      }
+    });
+    __syncthreads();
+    for (int i = tid; i < count; i += kSelThreads)
+      if (before + rank_in(i, 0, count) == e) {
+        thr_key[g] = list_key[i];
+        thr_tok[g] = list_tok[i];
+      }
+  }
+  __syncthreads();
+  each_again([&](u64 k, int t) {
+    const int bin = (int)((k - lo) >> shift);
+    int before = -1;  // keys before the bin, if it is one that did not fit
+    for (int g = 0; g < nb; ++g)
+      if (bin_of[g] == bin && slot_of[g] < 0) before = before_of[g];
+    if (before < 0) return;
+    int group = 0;
+    for (int g = 0; g < nb; ++g)
+      group += bin_of[g] == bin ? k > thr_key[g] || (k == thr_key[g] && t >= thr_tok[g]) : end_at[g] <= before;
+    budget[t] = budget_of[group];
+  });
 }
 
 // Token reordering plan: one workgroup walks the budgets twice in chunks of
@@ -397,9 +657,15 @@ hipError_t launch_permute_rows(const void* src, const int32_t* perm, long n_rows
 hipError_t launch_rank_budgets(const double* keys, long n_tokens, const GroupTable& tab,
                                int32_t* budget, hipStream_t s) {
   if (n_tokens <= 0) return hipSuccess;
-  const unsigned blocks = (unsigned)((n_tokens + kRankTokens - 1) / kRankTokens);
-  hipLaunchKernelGGL(rank_budgets, dim3(blocks), dim3(kThreads), 0, s,
-                     reinterpret_cast<const unsigned long long*>(keys), (int)n_tokens, tab, budget);
+  const auto* k = reinterpret_cast<const unsigned long long*>(keys);
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(1), dim3(kSelThreads), 0, s, k, (int)n_tokens, tab, budget);
+  };
+  const long per = (n_tokens + kSelThreads - 1) / kSelThreads;  // keys per thread
+  if (per <= 8) launch(select_budgets<8>);
+  else if (per <= 32) launch(select_budgets<32>);
+  else if (per <= 80) launch(select_budgets<80>);
+  else launch(select_budgets<0>);
   return hipGetLastError();
 }
 

@@ -89,3 +89,56 @@ def test_linear_f32_edges(m, n, k, option):
     bar = 2.0 ** -24 * (16 + 4 * k ** 0.5) * max(1.0, float(want.abs().max()))
     assert float((y[:m].cpu().double() - want).abs().max()) < bar
     assert torch.all(y[m] == 7.0)
+
+
+def _ranked_budgets(keys, groups):
+    """Budgets from the ascending order of (bit pattern, token), NaNs as one canonical NaN."""
+    keys = np.where(np.isnan(keys), np.float64("nan"), keys)
+    bits = keys.view(np.uint64)
+    budget = np.empty(len(keys), np.int32)
+    order = np.lexsort((np.arange(len(keys)), bits))
+    at = 0
+    for s, c in groups:
+        budget[order[at:at + c]] = s
+        at += c
+    return budget
+
+
+def _keys(pattern, n, rng):
+    k = rng.chisquare(64, n)
+    if pattern == "equal":
+        return np.full(n, 2.5)
+    if pattern == "two_values":
+        return np.where(rng.random(n) < 0.5, 1.0, 3.0)
+    if pattern == "outliers":  # the range spans every exponent, nearly all keys share a few bins
+        k[rng.integers(0, n, 3)] = (0.0, np.inf, np.nan)
+        return 1.0 + k * 1e-12
+    if pattern == "many_nan":
+        k[rng.random(n) < 0.6] = np.nan
+        return k
+    if pattern == "negative":
+        return k - 64
+    if pattern == "lognormal":
+        return np.exp(4 * rng.standard_normal(n))
+    return k
+
+
+# tokens around a wave, the workgroup, the list, the register-resident limit (32768)
+@pytest.mark.parametrize("n", [1, 2, 63, 1025, 4097, 32768, 32769, 75601])
+@pytest.mark.parametrize("pattern", ["chi2", "equal", "two_values", "outliers", "many_nan", "negative", "lognormal"])
+@pytest.mark.parametrize("n_groups", [1, 3, 16])
+def test_assign_budgets_by_key_edges(n, pattern, n_groups):
+    rng = np.random.default_rng(n * 31 + n_groups)
+    T = 2 ** 15
+    budgets = [2 ** i for i in range(n_groups)]
+    cuts = np.sort(rng.integers(0, n + 1, n_groups - 1))
+    if n_groups > 4:
+        cuts[3] = cuts[2]  # an empty group
+        cuts[0] = 0        # and an empty first group
+    sizes = np.diff(np.concatenate([[0], cuts, [n]]))
+    groups = list(zip(budgets, sizes.tolist()))
+    keys = _keys(pattern, n, rng)
+    out = torch.full((n + 1,), -5, dtype=torch.int32, device=DEV)
+    H.hsa_assign_budgets_by_key(torch.from_numpy(keys).to(DEV), T, groups, out[:n])
+    assert np.array_equal(out[:n].cpu().numpy(), _ranked_budgets(keys, groups))
+    assert int(out[n]) == -5
