@@ -142,3 +142,29 @@ def test_assign_budgets_by_key_edges(n, pattern, n_groups):
     H.hsa_assign_budgets_by_key(torch.from_numpy(keys).to(DEV), T, groups, out[:n])
     assert np.array_equal(out[:n].cpu().numpy(), _ranked_budgets(keys, groups))
     assert int(out[n]) == -5
+
+
+# tokens around the 64 of a workgroup, channels around the 64 of a chunk and off the 16-byte path
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 1000])
+@pytest.mark.parametrize("channels", [4, 16, 62, 64, 68, 200])
+def test_l1_rel_edges(n, channels):
+    rng = np.random.default_rng(n + channels)
+    v, p = (rng.standard_normal((n, channels)).astype(np.float32) for _ in range(2))
+    v[0] = 0.0  # x/0
+    acc0 = rng.random(n)
+    num, den = np.zeros(n), np.zeros(n)
+    for c in range(channels):  # float64 sums in channel order
+        num += np.abs(v[:, c].astype(np.float64) - p[:, c].astype(np.float64))
+        den += np.abs(v[:, c].astype(np.float64))
+    with np.errstate(divide="ignore"):
+        want = acc0 + num / den
+    tv, tp, ta = (torch.from_numpy(a.copy()).to(DEV) for a in (v, p, acc0))
+    H.hsa_l1_rel_accumulate(tv, tp, ta, False)
+    assert np.array_equal(ta.cpu().numpy(), want)
+    assert torch.equal(tp, tv)
+    H.hsa_l1_rel_accumulate(tv, tp, ta, False)  # no change since: 0/0 adds NaN, 0/x nothing
+    want[0] = np.nan
+    assert np.array_equal(ta.cpu().numpy(), want, equal_nan=True)
+    tp.zero_()
+    H.hsa_l1_rel_accumulate(tv, tp, ta, True)
+    assert torch.count_nonzero(ta) == 0 and torch.equal(tp, tv)
