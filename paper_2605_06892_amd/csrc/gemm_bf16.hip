@@ -8,23 +8,27 @@
 //     tokens fused into the epilogue.
 // The compact gathered activations are never materialized in HBM.
 //
-// Tiling (struct Tiling): BM x BN output tile per workgroup of 8 waves in a
-// WM x WN grid, K step 64, v_mfma_f32_32x32x16_bf16. Tiles go global -> LDS
+// Tiling (struct Tiling): BM x BN output tile per workgroup of waves in a
+// WM x WN grid, K step 64, v_mfma_f32_16x16x32_bf16. Tiles go global -> LDS
 // directly (buffer_load_dwordx4 ... lds through one buffer resource over A
 // and one over B, or global_load_lds_dwordx4 with 64-bit lane pointers for a
 // matrix of 4 GiB or more: one wave instruction fills one contiguous 1 KB
-// segment = 8 tile rows of 128 bytes) into two stages, the
-// loads of step k+1 in flight during the MFMAs of step k, one barrier per
-// step. Within a step the fragment reads of k slice s+1 and the stage loads
-// are placed one per MFMA between the MFMAs of slice s, so neither the LDS
-// latency nor the load issue stalls the matrix pipe (measured: issuing them
-// in bursts ahead of the MFMAs cost 5-10%), and the MFMAs of the last
-// slice's fragment rows (half of them at 256 x 256 with 64-bit pointers) run
-// behind the next step's barrier, where they cover that step's first reads. The 16-byte chunks of tile row r
+// segment = 8 tile rows of 128 bytes). The 16-byte chunks of tile row r
 // sit at slot chunk ^ ((r >> 1) & 7), which keeps the fragment reads (16
-// rows, one chunk) on disjoint banks. Each stage is its own LDS array and the
-// K loop is unrolled by the stage count, so the compiler can tell the
-// asynchronous loads from reads of the other stage.
+// rows, one chunk) on disjoint banks. Each LDS array is a variable of its own
+// and the K loops are unrolled by the array count, so the compiler can tell the
+// asynchronous loads from reads of another array.
+//
+// The large tilings (8 waves, 256 rows) run a ping-pong loop: while one of a
+// SIMD's two waves issues MFMAs and nothing else, the other reads its next
+// fragments and issues loads. With both waves doing both at once, interleaved
+// by the compiler around one barrier per step, the matrix pipes were busy 71%
+// of the Q/K/V launch at 8190 x 5120; they are now 80-83%. The 32x32x16 MFMA
+// then ran at a clock of 1.49 GHz (the card's power limit), 16x16x32 runs at
+// 1.61 GHz: it reads and writes half as many accumulators per product. Together
+// that launch went from 1045 to 884 us (1.23 -> 1.46 PFLOP/s), the output
+// projection of 16380 x 5120 from 667 to 550 us (1.56 PFLOP/s), the FFN's down
+// projection of 8190 x 8960 x 1536 from 176 to 148 us, with the same bits.
 // Every tile row is a contiguous 128-byte run of a token row, so the indexed
 // loads stay coalesced; rows outside the problem are read from a valid row and
 // their results dropped. The product is formed transposed (B rows drive the
@@ -45,6 +49,8 @@ typedef __attribute__((address_space(3))) void lds_void;
 typedef __attribute__((address_space(1))) const void global_cvoid;
 
 constexpr int waitcnt_vm(int n) { return (n & 15) | (7 << 4) | (15 << 8) | ((n >> 4) << 14); }
+
+constexpr int waitcnt_lgkm0() { return 15 | (7 << 4) | (0 << 8) | (3 << 14); }
 
 // f(integral_constant<int, I>) for I = B .. E-1, unrolled at compile time
 template <int B, int E, class F>
@@ -78,7 +84,8 @@ struct Tiling {
   static constexpr int BM = BM_, BN = BN_, BK = BK_, STAGES = STAGES_, WAVES = WAVES_, WM = WM_;
   static constexpr int WN = WAVES / WM, THREADS = WAVES * 64;
   static constexpr int TM = BM / WM, TN = BN / WN;  // wave tile
-  static constexpr int MI = TM / 32, NI = TN / 32;  // 32x32 MFMA tiles per wave
+  static constexpr int MI = TM / 16, NI = TN / 16;  // 16x16 MFMA tiles per wave
+  static constexpr int RB = TM / 32;                // 32-row blocks of the wave tile (epilogue)
   static constexpr int CHUNKS = BK / 8;             // 16-byte chunks per tile row
   static constexpr int SEG_ROWS = 64 / CHUNKS;      // tile rows per 1 KB wave load
   static constexpr int SEG_A = BM / SEG_ROWS, SEG_B = BN / SEG_ROWS;
@@ -86,7 +93,7 @@ struct Tiling {
   static constexpr int STAGE = (BM + BN) * BK;           // bf16 elements per stage
   static_assert(BK == 32 || BK == 64, "K step");
   static_assert(LOADS * WAVES == SEG_A + SEG_B && SEG_A % WAVES == 0, "stage load must split evenly over waves");
-  static_assert(MI * 32 == TM && NI * 32 == TN, "wave tile");
+  static_assert(RB * 32 == TM && NI * 16 == TN, "wave tile");
   static_assert(LOADS * (STAGES - 2 > 0 ? STAGES - 2 : 0) <= 63, "vmcnt range");
   static_assert(STAGES * STAGE * 2 <= 160 * 1024, "LDS");
   // 16-byte chunk c of tile row r sits at slot c ^ swz(r): any 16 consecutive
@@ -96,25 +103,30 @@ struct Tiling {
 };
 
 // Output tile (tm, tn) of output z in tiling TL, staged through the
-// workgroup's LDS arrays L0..L3 (at least TL::STAGE elements each, as many as
-// TL has stages). Each stage is its own array, so that the compiler can tell
-// the asynchronous loads into one stage from the fragment reads of another.
+// workgroup's LDS arrays: two A tiles and three B tiles, each an array of its
+// own, so that the compiler can tell the asynchronous loads into one from the
+// fragment reads of another.
 // BUF: stage loads through buffer resources (A and B each below 4 GiB), else
 // through 64-bit lane pointers. ROPE: the RoPE epilogue is compiled in (the
 // Q/K/V projection only).
-template <class TL, int EPI, bool BUF, bool ROPE, class LA, class LB, class LC, class LD>
-__device__ __forceinline__ void row_gemm_tile(const RowGemm& g, int tm, int tn, int z, LA& L0, LB& L1,
-                                              LC& L2, LD& L3) {
-  constexpr int BM = TL::BM, BN = TL::BN, BK = TL::BK, STAGES = TL::STAGES, WN = TL::WN;
-  constexpr int TM = TL::TM, TN = TL::TN, MI = TL::MI, NI = TL::NI, LOADS = TL::LOADS;
+constexpr int kTileElems = 256 * 64;  // elements of each LDS array (32 KB)
+typedef bf16 LdsTile[kTileElems];
+
+template <class TL, int EPI, bool BUF, bool ROPE>
+__device__ __forceinline__ void row_gemm_tile(const RowGemm& g, int tm, int tn, int z, LdsTile& A0, LdsTile& A1,
+                                              LdsTile& B0, LdsTile& B1, LdsTile& B2) {
+  constexpr int BM = TL::BM, BN = TL::BN, BK = TL::BK, WN = TL::WN;
+  constexpr int TM = TL::TM, TN = TL::TN, MI = TL::MI, NI = TL::NI, RB = TL::RB, LOADS = TL::LOADS;
   constexpr int SEG_A = TL::SEG_A, CHUNKS = TL::CHUNKS, SEG_ROWS = TL::SEG_ROWS;
-  auto stage = [&](auto s) -> bf16* {
-    if constexpr (decltype(s)::value == 0) return L0;
-    else if constexpr (decltype(s)::value == 1) return L1;
-    else if constexpr (decltype(s)::value == 2) return L2;
-    else return L3;
+  auto a_tile = [&](auto s) -> bf16* {
+    if constexpr (decltype(s)::value == 0) return A0;
+    else return A1;
   };
-  static_assert(STAGES >= 2 && STAGES <= 4, "stages");
+  auto b_tile = [&](auto s) -> bf16* {
+    if constexpr (decltype(s)::value == 0) return B0;
+    else if constexpr (decltype(s)::value == 1) return B1;
+    else return B2;
+  };
   const RowGemmOut oz = row_gemm_out(g, z);
 
   const bf16* __restrict__ A = static_cast<const bf16*>(g.A);
@@ -122,7 +134,7 @@ __device__ __forceinline__ void row_gemm_tile(const RowGemm& g, int tm, int tn, 
 
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wm = wave / WN, wn = wave % WN;
-  const int l32 = lane & 31, hi = lane >> 5;
+  const int l16 = lane & 15, grp = lane >> 4;
 
   // This lane's rows of the stage loads: segment s = i*WAVES + wave covers
   // tile rows SEG_ROWS*s .. (A tile first, then B tile); the lane fetches
@@ -130,7 +142,7 @@ __device__ __forceinline__ void row_gemm_tile(const RowGemm& g, int tm, int tn, 
   // into LDS slot lane%CHUNKS.
   const bf16* src[LOADS];  // !BUF: the lane's chunk of its row in A or B
   unsigned voff[LOADS];    // BUF: the same as a byte offset from A or B
-  int dst[LOADS];          // element offset of the segment in its stage
+  int dst[LOADS];          // element offset of the segment in its tile
 #pragma unroll
   for (int i = 0; i < LOADS; ++i) {
     const int s = i * TL::WAVES + wave;
@@ -151,165 +163,148 @@ __device__ __forceinline__ void row_gemm_tile(const RowGemm& g, int tm, int tn, 
       voff[i] = (unsigned)((grow + chunk * 8) * 2);
     else
       src[i] = (a ? A : B) + grow + chunk * 8;
-    dst[i] = s * 512;  // the B tile follows the A tile in the stage
+    dst[i] = (a ? s : s - SEG_A) * 512;
   }
   // segment i of every wave lies in A when i * WAVES < SEG_A (SEG_A is a
   // multiple of WAVES), so the resource of a load is known at compile time
   const unsigned a_bytes = (unsigned)((long)g.a_limit * g.lda * 2), b_bytes = (unsigned)((long)g.Nc * g.ldb * 2);
-  auto issue = [&](auto st, int k0) -> void {
-#pragma unroll
-    for (int i = 0; i < LOADS; ++i) {
-      if constexpr (BUF) {
-        if (i * TL::WAVES < SEG_A)
-          buffer_load_lds16(A, a_bytes, stage(st) + dst[i], voff[i], (unsigned)(k0 * 2));
-        else
-          buffer_load_lds16(B, b_bytes, stage(st) + dst[i], voff[i], (unsigned)(k0 * 2));
-      } else {
-        __builtin_amdgcn_global_load_lds((global_cvoid*)(src[i] + k0), (lds_void*)(stage(st) + dst[i]), 16, 0, 0);
-      }
+  constexpr int LOADS_A = SEG_A / TL::WAVES, LOADS_B = LOADS - LOADS_A;
+  auto load = [&](bf16* tile, int i, int k0) __attribute__((always_inline)) {
+    if constexpr (BUF) {
+      if (i < LOADS_A)
+        buffer_load_lds16(A, a_bytes, tile + dst[i], voff[i], (unsigned)(k0 * 2));
+      else
+        buffer_load_lds16(B, b_bytes, tile + dst[i], voff[i], (unsigned)(k0 * 2));
+    } else {
+      __builtin_amdgcn_global_load_lds((global_cvoid*)(src[i] + k0), (lds_void*)(tile + dst[i]), 16, 0, 0);
     }
   };
+  auto issue_a = [&](auto st, int k0) {
+#pragma unroll
+    for (int i = 0; i < LOADS_A; ++i) load(a_tile(st), i, k0);
+  };
+  auto issue_b = [&](auto st, int k0) {
+#pragma unroll
+    for (int i = LOADS_A; i < LOADS; ++i) load(b_tile(st), i, k0);
+  };
 
-  // fragment read offsets: row (tile-local) l32 + 32*t, chunk kk*2 + hi;
-  // swz(l32 + 32 t) = swz(l32)
-  const int xr = ((hi ^ TL::swz(l32)) * 8);
-  f32x16 acc[MI][NI];
+  // fragment read offsets: row (tile-local) l16 + 16*t, chunk half*4 + grp;
+  // swz(l16 + 16 t) = swz(l16)
+  const int xr = ((grp ^ TL::swz(l16)) * 8);
+  f32x4 acc[MI][NI];
 #pragma unroll
   for (int i = 0; i < MI; ++i)
 #pragma unroll
-    for (int j = 0; j < NI; ++j) acc[i][j] = (f32x16){};
+    for (int j = 0; j < NI; ++j) acc[i][j] = (f32x4){};
 
-  // Fragments live in two register buffers: slice kk of a stage goes to
-  // buffer kk & 1, so a stage's last slice is in buffer 1. The MFMAs of its
-  // last DEF fragment rows are deferred to the start of the next stage's
-  // compute, behind the barrier: they need registers only, and they keep the
-  // matrix pipe busy while the next stage's first fragment reads are in
-  // flight (otherwise every wave waits for them right after the barrier).
-  // DEF is all rows, except at four row tiles per wave with 64-bit lane
-  // pointers for the loads: there only half of them fit in 256 registers
-  // (the buffer-resource loads free the registers for all of them: 1.6-2.5%
-  // faster). Buffer 1 starts at zero, so the first stage's deferred MFMAs add
-  // exact zeros.
-  bf16x8 af[2][MI], bfr[2][NI];
+  // Ping-pong K loop. Waves w and w + 4 share a SIMD; the waves of one half
+  // read fragments and issue tile loads while the other half's run MFMAs and
+  // nothing else, and a barrier swaps the roles. Step k of a wave takes four
+  // slots, two of each kind, each over half of the step's k:
+  //   M0  issue the loads of A for step k+1 (its array was last read in the
+  //       other half's M1 of step k-1, one slot ago); read the fragments of
+  //       k slices 0 and 1
+  //   C0  their MFMAs
+  //   M1  issue the loads of B for step k+2; read k slices 2 and 3
+  //   C1  their MFMAs
+  // Waves 4-7 run one slot behind. Step k+1's tiles must have landed before
+  // waves 0-3 enter its M0: waves 0-3 wait for their loads at the end of C1,
+  // waves 4-7 at the end of M1 (the same slot); the loads of B for step k+2
+  // stay in flight.
+  static_assert(BK == 64 && TL::WAVES == 8, "ping-pong: two halves of four waves, four k slices");
+  bf16x8 af[MI], bfr[NI];
+  auto barrier = [&]() {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_barrier" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto read = [&](auto as, auto bs, int half) {
+    const int off = (half * 32) ^ xr;
+    const bf16* Ar = a_tile(as) + (wm * TM + l16) * BK + off;
+    const bf16* Br = b_tile(bs) + (wn * TN + l16) * BK + off;
 #pragma unroll
-  for (int i = 0; i < MI; ++i) af[1][i] = (bf16x8){};
+    for (int j = 0; j < NI; ++j) bfr[j] = *reinterpret_cast<const bf16x8*>(Br + j * 16 * BK);
 #pragma unroll
-  for (int j = 0; j < NI; ++j) bfr[1][j] = (bf16x8){};
-  constexpr int DEF = (MI <= 2 || BUF) ? MI : MI / 2;
-  // the MFMAs of fragment rows i0 .. i1-1 of buffer b
-  auto mfmas = [&](auto bc, auto i0c, auto i1c) {
-    constexpr int b = decltype(bc)::value, i0 = decltype(i0c)::value, i1 = decltype(i1c)::value;
+    for (int i = 0; i < MI; ++i) af[i] = *reinterpret_cast<const bf16x8*>(Ar + i * 16 * BK);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto read_done = [&]() { __builtin_amdgcn_sched_barrier(0); __builtin_amdgcn_s_waitcnt(waitcnt_lgkm0()); };
+  auto mfmas = [&]() {
 #pragma unroll
-    for (int i = i0; i < i1; ++i)
+    for (int i = 0; i < MI; ++i)
 #pragma unroll
       for (int j = 0; j < NI; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[b][j], af[b][i], acc[i][j], 0, 0, 0);
-  };
-  auto compute = [&](auto st, auto lg) {
-    constexpr int LG = decltype(lg)::value, KS = BK / 16, R = MI + NI, M = MI * NI;
-    static_assert(M >= R, "one MFMA per fragment read at least");
-    static_assert(KS % 2 == 0, "the last slice of a stage is in buffer 1");
-    const bf16* As = stage(st) + (wm * TM + l32) * BK;
-    const bf16* Bs = stage(st) + BM * BK + (wn * TN + l32) * BK;
-    auto ld = [&](int kk, int b) {
-      const int off = (kk * 16) ^ xr;
-#pragma unroll
-      for (int i = 0; i < MI; ++i) af[b][i] = *reinterpret_cast<const bf16x8*>(As + i * 32 * BK + off);
-#pragma unroll
-      for (int j = 0; j < NI; ++j) bfr[b][j] = *reinterpret_cast<const bf16x8*>(Bs + j * 32 * BK + off);
-    };
-    ld(0, 0);
-    // the previous stage's deferred rows, then this stage's slices 0 .. KS-2
-    // with the reads of each next slice and the stage loads between the MFMAs
-    mfmas(std::integral_constant<int, 1>{}, std::integral_constant<int, MI - DEF>{},
-          std::integral_constant<int, MI>{});
-    __builtin_amdgcn_sched_group_barrier(0x100, R, 0);
-    static_for<0, DEF * NI>([&](auto mc) {
-      constexpr int m = decltype(mc)::value;
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-      if constexpr (m < LG) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
-    });
-    static_for<0, KS - 1>([&](auto kc) {
-      constexpr int kk = decltype(kc)::value;
-      ld(kk + 1, (kk + 1) & 1);
-      mfmas(std::integral_constant<int, kk & 1>{}, std::integral_constant<int, 0>{},
-            std::integral_constant<int, MI>{});
-      static_for<0, M>([&](auto mc) {
-        constexpr int m = decltype(mc)::value;
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        if constexpr (m < R) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-        if constexpr (DEF * NI + kk * M + m < LG) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
-      });
-    });
-    // slice KS-1: the rows before the deferred ones
-    mfmas(std::integral_constant<int, 1>{}, std::integral_constant<int, 0>{},
-          std::integral_constant<int, MI - DEF>{});
-    static_for<0, (MI - DEF) * NI>([&](auto mc) { __builtin_amdgcn_sched_group_barrier(0x008, 1, 0); });
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[j], af[i], acc[i][j], 0, 0, 0);
   };
 
+  const int nk = g.K / BK;
+  // The loads past the last step repeat its own (their lines are in L2 and
+  // nobody reads the copies): every step then has the same loads and waits, so
+  // that the compiler adds none of its own.
+  auto step = [&](auto uc, int k, auto late) __attribute__((always_inline)) {
+    constexpr int u = decltype(uc)::value;
+    using SA = std::integral_constant<int, u % 2>;
+    using NA = std::integral_constant<int, (u + 1) % 2>;
+    using SB = std::integral_constant<int, u % 3>;
+    using NB = std::integral_constant<int, (u + 2) % 3>;
+    read(SA{}, SB{}, 0);
+    issue_a(NA{}, min(k + 1, nk - 1) * BK);
+    read_done();
+    barrier();
+    mfmas();
+    barrier();
+    read(SA{}, SB{}, 1);
+    issue_b(NB{}, min(k + 2, nk - 1) * BK);
+    read_done();
+    if constexpr (decltype(late)::value) __builtin_amdgcn_s_waitcnt(waitcnt_vm(LOADS_B));
+    barrier();
+    mfmas();
+    if constexpr (!decltype(late)::value) __builtin_amdgcn_s_waitcnt(waitcnt_vm(LOADS_B));
+    barrier();
+  };
+  // all steps of one half of the waves (a loop of its own for each half)
+  auto steps = [&](auto late) __attribute__((always_inline)) {
+    int k = 0;
+    while (true) {
+      step(std::integral_constant<int, 0>{}, k, late);
+      if (++k == nk) break;
+      step(std::integral_constant<int, 1>{}, k, late);
+      if (++k == nk) break;
+      step(std::integral_constant<int, 2>{}, k, late);
+      if (++k == nk) break;
+      step(std::integral_constant<int, 3>{}, k, late);
+      if (++k == nk) break;
+      step(std::integral_constant<int, 4>{}, k, late);
+      if (++k == nk) break;
+      step(std::integral_constant<int, 5>{}, k, late);
+      if (++k == nk) break;
+    }
+  };
   using S0 = std::integral_constant<int, 0>;
   using S1 = std::integral_constant<int, 1>;
-  using S2 = std::integral_constant<int, 2 % STAGES>;
-  using S3 = std::integral_constant<int, 3 % STAGES>;
-  using Interleave = std::integral_constant<int, LOADS>;
-  using NoLoads = std::integral_constant<int, 0>;
-  const int nk = g.K / BK;
-  // prologue: steps 0 .. STAGES-2 in flight
-  issue(S0{}, 0);
-  if constexpr (STAGES > 2) if (1 < nk) issue(S1{}, BK);
-  if constexpr (STAGES > 3) if (2 < nk) issue(S2{}, 2 * BK);
-  // step k lives in stage k % STAGES: wait for its loads (the loads of the
-  // up to STAGES-2 later steps may stay in flight; loads complete in order),
-  // make them visible to all waves (which also frees stage (k-1) % STAGES),
-  // start step k+STAGES-1's loads into that stage, compute step k. In the
-  // steady state (full) the loads are unconditional and share the scheduling
-  // region of the MFMAs; near the end of K they are conditional.
-  auto step = [&](auto st, auto nxt, int k, auto full) {
-    if (STAGES > 2 && k + STAGES - 2 < nk) __builtin_amdgcn_s_waitcnt(waitcnt_vm(LOADS * (STAGES > 2 ? STAGES - 2 : 0)));
-    else __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
-    __syncthreads();
-    if constexpr (decltype(full)::value) {
-      issue(nxt, (k + STAGES - 1) * BK);
-      compute(st, Interleave{});
-    } else {
-      if (k + STAGES - 1 < nk) issue(nxt, (k + STAGES - 1) * BK);
-      compute(st, NoLoads{});
-    }
-  };
-  // nxt = (k + STAGES - 1) % STAGES = (k - 1) % STAGES. Whole rounds of
-  // STAGES steps whose loads all fall inside K run in the loop, the remaining
-  // steps after it, so that the loop body has no conditional step (the
-  // accumulators stay in place).
-  auto round = [&](int k, int n, auto full) __attribute__((always_inline)) {
-    if constexpr (STAGES == 2) {
-      step(S0{}, S1{}, k, full);
-      if (n > 1) step(S1{}, S0{}, k + 1, full);
-    } else if constexpr (STAGES == 3) {
-      step(S0{}, S2{}, k, full);
-      if (n > 1) step(S1{}, S0{}, k + 1, full);
-      if (n > 2) step(S2{}, S1{}, k + 2, full);
-    } else {
-      step(S0{}, S3{}, k, full);
-      if (n > 1) step(S1{}, S0{}, k + 1, full);
-      if (n > 2) step(S2{}, S1{}, k + 2, full);
-      if (n > 3) step(S3{}, S2{}, k + 3, full);
-    }
-  };
-  int k = 0;
-  for (; k + 2 * STAGES - 1 <= nk; k += STAGES) round(k, STAGES, std::true_type{});
-  for (; k < nk; k += STAGES) round(k, min(STAGES, nk - k), std::false_type{});
-  mfmas(std::integral_constant<int, 1>{}, std::integral_constant<int, MI - DEF>{},
-        std::integral_constant<int, MI>{});  // the last stage's deferred rows
+  issue_b(S0{}, 0);
+  issue_a(S0{}, 0);
+  issue_b(S1{}, min(1, nk - 1) * BK);
+  __builtin_amdgcn_s_waitcnt(waitcnt_vm(LOADS_B));
+  barrier();
+  if (__builtin_amdgcn_readfirstlane(wave) >= 4) {
+    barrier();
+    steps(std::true_type{});
+  } else {
+    steps(std::false_type{});
+    barrier();
+  }
+  __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));  // the repeated loads, before the epilogue takes the arrays
 
-  // Epilogue through LDS. acc[i][j][e] is output row (tile row + i*32 + l32),
-  // column (tile col + j*32 + (e/4)*8 + hi*4 + e%4): a lane holds 4 columns
+  // Epilogue through LDS. acc[i][j][e] is output row (tile row + i*16 + l16),
+  // column (tile col + j*16 + grp*4 + e): a lane holds 4 columns
   // of one row, so direct stores would write 16-byte pieces of 32 rows per
   // instruction. Instead, for each 32-row block i, every wave writes its
   // fp32 values (row scale, RoPE and GELU applied) to its own LDS region,
   // then reads them back row-contiguous, 4 columns per lane (the residual is
   // added there, then the value rounded once), and stores runs of 4 columns
-  // per lane, 128 bytes or more per row. Waves 0-3 use the first stage's
-  // array, 4-7 the second; the scatter target of each row travels through
+  // per lane, 128 bytes or more per row. Two or more waves share an
+  // LDS array; the scatter target of each row travels through
   // LDS too. Every global load of the epilogue (row indices, row scales,
   // RoPE positions and angles, residuals) precedes its first store: the
   // results of all blocks are held in registers and stored after the last
@@ -319,19 +314,20 @@ __device__ __forceinline__ void row_gemm_tile(const RowGemm& g, int tm, int tn, 
   constexpr int TNP = TN + 4;         // padded staging row, floats
   constexpr int QPR = TN / 4;         // 4-column groups per row
   constexpr int NT = QPR / 2;         // read-back passes of the wave per block
-  constexpr int REGION = 32 * TNP * 4 + MI * 32 * (8 + 4);
-  static_assert(4 * REGION <= TL::STAGE * 2, "epilogue staging must fit in a stage");
+  constexpr int REGION = 32 * TNP * 4 + TM * (8 + 4);
+  static_assert(2 * REGION <= kTileElems * 2, "the staging of two waves must fit in an LDS array");
   static_assert(QPR % 2 == 0, "the wave covers whole rows in each read-back pass");
   __syncthreads();  // every wave is done with the stages
-  char* region = reinterpret_cast<char*>((wave < 4) ? L0 : L1) + (wave % 4) * REGION;
+  bf16* staging = wave < 4 ? (wave < 2 ? A0 : A1) : (wave < 6 ? B0 : B1);
+  char* region = reinterpret_cast<char*>(staging) + (wave % 2) * REGION;
   float* blk = reinterpret_cast<float*>(region);
   // per block i, row r: output element offset and target (0: C, 1: C2, -1: none)
   long* row_off = reinterpret_cast<long*>(region + 32 * TNP * 4);
-  int* row_buf = reinterpret_cast<int*>(region + 32 * TNP * 4 + MI * 32 * 8);
+  int* row_buf = reinterpret_cast<int*>(region + 32 * TNP * 4 + TM * 8);
   const int32_t* c_rows = oz.c_rows;
   const bool rope = ROPE && g.rope_cs && ((g.rope_outs >> z) & 1);
   const int col0 = tn * BN + wn * TN;  // first output column of the wave tile
-  const int m0 = tm * BM + wm * TM + l32;  // the lane's row in block 0
+  const int m0 = tm * BM + wm * TM + l16;  // the lane's row in row tile 0
   int crow[MI];
   float rs[MI];
   RopeRow rr[MI];
@@ -341,7 +337,7 @@ __device__ __forceinline__ void row_gemm_tile(const RowGemm& g, int tm, int tn, 
   // selected afterwards.
 #pragma unroll
   for (int i = 0; i < MI; ++i) {
-    const int m = m0 + i * 32;
+    const int m = m0 + i * 16;
     const int mc = min(m, g.M - 1);
     const int cr = c_rows ? c_rows[mc] : m;
     crow[i] = m < g.M ? cr : -1;
@@ -358,16 +354,16 @@ __device__ __forceinline__ void row_gemm_tile(const RowGemm& g, int tm, int tn, 
       buf = second ? 1 : 0;
       obase = (long)(second ? crow[i] - oz.c_split : crow[i]) * g.ldc;
     }
-    if (hi == 0) {
-      row_off[i * 32 + l32] = obase;
-      row_buf[i * 32 + l32] = buf;
+    if (grp == 0) {
+      row_off[i * 16 + l16] = obase;
+      row_buf[i * 16 + l16] = buf;
     }
   }
   __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");  // the row tables are visible
   typedef typename std::conditional<EPI == kEpiF32, f32x4, bf16x4>::type OutT;
-  OutT ov[MI][NT];  // block i, read-back pass t: the lane's 4 output values
+  OutT ov[RB][NT];  // block i, read-back pass t: the lane's 4 output values
 #pragma unroll
-  for (int i = 0; i < MI; ++i) {
+  for (int i = 0; i < RB; ++i) {
     if constexpr (EPI == kEpiBf16Residual) {  // the residual first takes the output's place
       __builtin_amdgcn_sched_barrier(0);  // one block's residuals at a time (registers)
       bool in[NT];
@@ -390,36 +386,34 @@ __device__ __forceinline__ void row_gemm_tile(const RowGemm& g, int tm, int tn, 
         if (!in[t]) ov[i][t] = (bf16x4){};
       }
     }
-    // the block's RoPE angles, all loaded before any is used (every index is
-    // in the table, so the loads need no condition)
-    f32x2 cs[NI][4][2];
-    if (rope) {
 #pragma unroll
-      for (int j = 0; j < NI; ++j)
+    for (int h = 0; h < 2; ++h) {
+      const int it = 2 * i + h;  // row tile
+      // its RoPE angles, all loaded before any is used (every index is in the
+      // table, so the loads need no condition)
+      f32x2 cs[NI][2];
+      if (rope) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int k = ((col0 + j * 32 + q * 8 + hi * 4) % g.rope_dh) >> 1;
-          cs[j][q][0] = rope_angle(g, rr[i], k);
-          cs[j][q][1] = rope_angle(g, rr[i], k + 1);
+        for (int j = 0; j < NI; ++j) {
+          const int k = ((col0 + j * 16 + grp * 4) % g.rope_dh) >> 1;
+          cs[j][0] = rope_angle(g, rr[it], k);
+          cs[j][1] = rope_angle(g, rr[it], k + 1);
         }
-    }
+      }
 #pragma unroll
-    for (int j = 0; j < NI; ++j) {
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int c = j * 32 + q * 8 + hi * 4;
-        f32x4 v = {acc[i][j][4 * q + 0], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
-        if (g.row_scale) v *= rs[i];
+      for (int j = 0; j < NI; ++j) {
+        f32x4 v = acc[it][j];
+        if (g.row_scale) v *= rs[it];
         if (rope) {
-          const f32x2 r0 = rope_rotate(cs[j][q][0], v[0], v[1]);
-          const f32x2 r1 = rope_rotate(cs[j][q][1], v[2], v[3]);
+          const f32x2 r0 = rope_rotate(cs[j][0], v[0], v[1]);
+          const f32x2 r1 = rope_rotate(cs[j][1], v[2], v[3]);
           v = (f32x4){r0[0], r0[1], r1[0], r1[1]};
         }
         if constexpr (EPI == kEpiBf16Gelu) {
 #pragma unroll
           for (int u = 0; u < 4; ++u) v[u] = gelu_tanh(v[u]);
         }
-        *reinterpret_cast<f32x4*>(blk + l32 * TNP + c) = v;
+        *reinterpret_cast<f32x4*>(blk + (h * 16 + l16) * TNP + j * 16 + grp * 4) = v;
       }
     }
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
@@ -443,7 +437,7 @@ __device__ __forceinline__ void row_gemm_tile(const RowGemm& g, int tm, int tn, 
   // registers and spill
   asm volatile("" ::: "memory");
 #pragma unroll
-  for (int i = 0; i < MI; ++i) {
+  for (int i = 0; i < RB; ++i) {
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
       const int f = lane + 64 * t;
@@ -476,13 +470,9 @@ using TMid = Tiling<256, 128, 64, 2, 8, 4>;
 // one round of halves.
 template <class TL, int NOUT, int EPI, bool BUF>
 __global__ __launch_bounds__(TL::THREADS) void row_gemm_bf16_kernel(RowGemm g) {
-  constexpr int STAGES = TL::STAGES;
   constexpr bool kSplit = std::is_same<TL, TBig>::value;
-  static_assert(!kSplit || (TMid::STAGE <= TL::STAGE && TMid::THREADS == TL::THREADS), "halves");
-  __shared__ __attribute__((aligned(16))) bf16 L0[TL::STAGE];
-  __shared__ __attribute__((aligned(16))) bf16 L1[TL::STAGE];
-  __shared__ __attribute__((aligned(16))) bf16 L2[STAGES > 2 ? TL::STAGE : 1];
-  __shared__ __attribute__((aligned(16))) bf16 L3[STAGES > 3 ? TL::STAGE : 1];
+  static_assert(!kSplit || TMid::THREADS == TL::THREADS, "halves");
+  __shared__ __attribute__((aligned(16))) LdsTile A0, A1, B0, B1, B2;
 
   const int tiles_m = (g.M + TL::BM - 1) / TL::BM;
   const int tiles_n1 = (g.Nc + TL::BN - 1) / TL::BN;  // per output
@@ -506,11 +496,11 @@ __global__ __launch_bounds__(TL::THREADS) void row_gemm_bf16_kernel(RowGemm g) {
   const int tn = tnc - z * tiles_n1;
   if constexpr (kSplit) {
     if (half >= 0) {
-      row_gemm_tile<TMid, EPI, BUF, NOUT == 3>(g, tm, tn * 2 + half, z, L0, L1, L2, L3);
+      row_gemm_tile<TMid, EPI, BUF, NOUT == 3>(g, tm, tn * 2 + half, z, A0, A1, B0, B1, B2);
       return;
     }
   }
-  row_gemm_tile<TL, EPI, BUF, NOUT == 3>(g, tm, tn, z, L0, L1, L2, L3);
+  row_gemm_tile<TL, EPI, BUF, NOUT == 3>(g, tm, tn, z, A0, A1, B0, B1, B2);
 }
 
 // Rounds of a launch of `tiles` tiles on the CUs, in units of a full round
