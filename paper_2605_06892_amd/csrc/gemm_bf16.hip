@@ -29,6 +29,13 @@
 // that launch went from 1045 to 884 us (1.23 -> 1.46 PFLOP/s), the output
 // projection of 16380 x 5120 from 667 to 550 us (1.56 PFLOP/s), the FFN's down
 // projection of 8190 x 8960 x 1536 from 176 to 148 us, with the same bits.
+//
+// The small tilings run a ring of four arrays, loaded three steps ahead, with
+// one barrier per step: launches of few rows or columns are bound by the
+// latency of one workgroup's chain of steps, which a smaller tile shortens, and
+// by the CUs left without a workgroup. 400 x 8960 x 1536 products went from 100
+// to 38 us, 1000 x 1536 x 1536 from 20.5 to 9.8 us, and those of a block of 500
+// rows at d = 256 from 8.5-12 to 5-6 us (kernel alone).
 // Every tile row is a contiguous 128-byte run of a token row, so the indexed
 // loads stay coalesced; rows outside the problem are read from a valid row and
 // their results dropped. The product is formed transposed (B rows drive the
@@ -51,6 +58,9 @@ typedef __attribute__((address_space(1))) const void global_cvoid;
 constexpr int waitcnt_vm(int n) { return (n & 15) | (7 << 4) | (15 << 8) | ((n >> 4) << 14); }
 
 constexpr int waitcnt_lgkm0() { return 15 | (7 << 4) | (0 << 8) | (3 << 14); }
+
+template <int I>
+using Int = std::integral_constant<int, I>;
 
 // f(integral_constant<int, I>) for I = B .. E-1, unrolled at compile time
 template <int B, int E, class F>
@@ -76,9 +86,10 @@ __device__ __forceinline__ void buffer_load_lds16(const void* base, unsigned nby
   __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void*)dst, 16, voff, soff, 0, 0);
 }
 
-// One tiling of the kernel: BM x BN output tile, K step BK (32 or 64),
-// STAGES LDS stages (loads run STAGES-1 steps ahead), WAVES waves in a
-// WM x (WAVES/WM) grid.
+// One tiling of the kernel: BM x BN output tile, K step BK, WAVES waves in a
+// WM x (WAVES/WM) grid. STAGES 0: the ping-pong loop of 8 waves (two LDS arrays
+// for A tiles, three for B tiles); else a ring of STAGES arrays, each an A tile
+// followed by a B tile, loaded STAGES-1 steps ahead.
 template <int BM_, int BN_, int BK_, int STAGES_, int WAVES_, int WM_>
 struct Tiling {
   static constexpr int BM = BM_, BN = BN_, BK = BK_, STAGES = STAGES_, WAVES = WAVES_, WM = WM_;
@@ -90,12 +101,15 @@ struct Tiling {
   static constexpr int SEG_ROWS = 64 / CHUNKS;      // tile rows per 1 KB wave load
   static constexpr int SEG_A = BM / SEG_ROWS, SEG_B = BN / SEG_ROWS;
   static constexpr int LOADS = (SEG_A + SEG_B) / WAVES;  // load instructions per lane per stage
-  static constexpr int STAGE = (BM + BN) * BK;           // bf16 elements per stage
-  static_assert(BK == 32 || BK == 64, "K step");
+  static constexpr bool PING = STAGES == 0;
+  static constexpr int ARRAYS = PING ? 5 : STAGES;                        // LDS arrays
+  static constexpr int ARRAY = PING ? 256 * BK : (BM + BN) * BK;          // bf16 elements of each
+  static_assert(BK == 64, "K step");
   static_assert(LOADS * WAVES == SEG_A + SEG_B && SEG_A % WAVES == 0, "stage load must split evenly over waves");
   static_assert(RB * 32 == TM && NI * 16 == TN, "wave tile");
-  static_assert(LOADS * (STAGES - 2 > 0 ? STAGES - 2 : 0) <= 63, "vmcnt range");
-  static_assert(STAGES * STAGE * 2 <= 160 * 1024, "LDS");
+  static_assert(!PING || (WAVES == 8 && BM <= 256 && BN <= 256), "ping-pong: two halves of four waves");
+  static_assert(PING || (STAGES >= 2 && STAGES <= 4 && LOADS * (STAGES - 2) <= 63), "ring, vmcnt range");
+  static_assert(ARRAYS * ARRAY * 2 <= 160 * 1024, "LDS");
   // 16-byte chunk c of tile row r sits at slot c ^ swz(r): any 16 consecutive
   // rows read at one chunk (one fragment read, 256 bytes per 16 lanes) land
   // on 16 distinct 16-byte bank groups
@@ -103,30 +117,24 @@ struct Tiling {
 };
 
 // Output tile (tm, tn) of output z in tiling TL, staged through the
-// workgroup's LDS arrays: two A tiles and three B tiles, each an array of its
-// own, so that the compiler can tell the asynchronous loads into one from the
-// fragment reads of another.
+// workgroup's LDS arrays, separate arrays, so that the compiler can tell the
+// asynchronous loads into one from the fragment reads of another.
 // BUF: stage loads through buffer resources (A and B each below 4 GiB), else
 // through 64-bit lane pointers. ROPE: the RoPE epilogue is compiled in (the
 // Q/K/V projection only).
-constexpr int kTileElems = 256 * 64;  // elements of each LDS array (32 KB)
-typedef bf16 LdsTile[kTileElems];
+struct LdsArrays {
+  bf16* p[5];
+};
 
 template <class TL, int EPI, bool BUF, bool ROPE>
-__device__ __forceinline__ void row_gemm_tile(const RowGemm& g, int tm, int tn, int z, LdsTile& A0, LdsTile& A1,
-                                              LdsTile& B0, LdsTile& B1, LdsTile& B2) {
+__device__ __forceinline__ void row_gemm_tile(const RowGemm& g, int tm, int tn, int z, const LdsArrays& lds) {
   constexpr int BM = TL::BM, BN = TL::BN, BK = TL::BK, WN = TL::WN;
   constexpr int TM = TL::TM, TN = TL::TN, MI = TL::MI, NI = TL::NI, RB = TL::RB, LOADS = TL::LOADS;
   constexpr int SEG_A = TL::SEG_A, CHUNKS = TL::CHUNKS, SEG_ROWS = TL::SEG_ROWS;
-  auto a_tile = [&](auto s) -> bf16* {
-    if constexpr (decltype(s)::value == 0) return A0;
-    else return A1;
-  };
-  auto b_tile = [&](auto s) -> bf16* {
-    if constexpr (decltype(s)::value == 0) return B0;
-    else if constexpr (decltype(s)::value == 1) return B1;
-    else return B2;
-  };
+  constexpr int RING = TL::PING ? 1 : TL::STAGES;
+  // the arrays of step u's A and B tiles (in a ring, those of stage u)
+  auto a_tile = [&](int u) -> bf16* { return TL::PING ? lds.p[u % 2] : lds.p[u % RING]; };
+  auto b_tile = [&](int u) -> bf16* { return TL::PING ? lds.p[2 + u % 3] : lds.p[u % RING] + BM * BK; };
   const RowGemmOut oz = row_gemm_out(g, z);
 
   const bf16* __restrict__ A = static_cast<const bf16*>(g.A);
@@ -181,11 +189,11 @@ __device__ __forceinline__ void row_gemm_tile(const RowGemm& g, int tm, int tn, 
   };
   auto issue_a = [&](auto st, int k0) {
 #pragma unroll
-    for (int i = 0; i < LOADS_A; ++i) load(a_tile(st), i, k0);
+    for (int i = 0; i < LOADS_A; ++i) load(a_tile(decltype(st)::value), i, k0);
   };
   auto issue_b = [&](auto st, int k0) {
 #pragma unroll
-    for (int i = LOADS_A; i < LOADS; ++i) load(b_tile(st), i, k0);
+    for (int i = LOADS_A; i < LOADS; ++i) load(b_tile(decltype(st)::value), i, k0);
   };
 
   // fragment read offsets: row (tile-local) l16 + 16*t, chunk half*4 + grp;
@@ -197,39 +205,29 @@ __device__ __forceinline__ void row_gemm_tile(const RowGemm& g, int tm, int tn, 
 #pragma unroll
     for (int j = 0; j < NI; ++j) acc[i][j] = (f32x4){};
 
-  // Ping-pong K loop. Waves w and w + 4 share a SIMD; the waves of one half
-  // read fragments and issue tile loads while the other half's run MFMAs and
-  // nothing else, and a barrier swaps the roles. Step k of a wave takes four
-  // slots, two of each kind, each over half of the step's k:
-  //   M0  issue the loads of A for step k+1 (its array was last read in the
-  //       other half's M1 of step k-1, one slot ago); read the fragments of
-  //       k slices 0 and 1
-  //   C0  their MFMAs
-  //   M1  issue the loads of B for step k+2; read k slices 2 and 3
-  //   C1  their MFMAs
-  // Waves 4-7 run one slot behind. Step k+1's tiles must have landed before
-  // waves 0-3 enter its M0: waves 0-3 wait for their loads at the end of C1,
-  // waves 4-7 at the end of M1 (the same slot); the loads of B for step k+2
-  // stay in flight.
-  static_assert(BK == 64 && TL::WAVES == 8, "ping-pong: two halves of four waves, four k slices");
   bf16x8 af[MI], bfr[NI];
   auto barrier = [&]() {
     __builtin_amdgcn_sched_barrier(0);
     asm volatile("s_barrier" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
   };
-  auto read = [&](auto as, auto bs, int half) {
+  // the fragments of half a K step (32 k) of step u
+  auto read = [&](auto uc, int half) __attribute__((always_inline)) {
     const int off = (half * 32) ^ xr;
-    const bf16* Ar = a_tile(as) + (wm * TM + l16) * BK + off;
-    const bf16* Br = b_tile(bs) + (wn * TN + l16) * BK + off;
+    const bf16* Ar = a_tile(decltype(uc)::value) + (wm * TM + l16) * BK + off;
+    const bf16* Br = b_tile(decltype(uc)::value) + (wn * TN + l16) * BK + off;
 #pragma unroll
     for (int j = 0; j < NI; ++j) bfr[j] = *reinterpret_cast<const bf16x8*>(Br + j * 16 * BK);
 #pragma unroll
     for (int i = 0; i < MI; ++i) af[i] = *reinterpret_cast<const bf16x8*>(Ar + i * 16 * BK);
     __builtin_amdgcn_sched_barrier(0);
   };
-  auto read_done = [&]() { __builtin_amdgcn_sched_barrier(0); __builtin_amdgcn_s_waitcnt(waitcnt_lgkm0()); };
-  auto mfmas = [&]() {
+  // the reads are done: the arrays may be rewritten after the next barrier
+  auto read_done = [&]() {
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(waitcnt_lgkm0());
+  };
+  auto mfmas = [&]() __attribute__((always_inline)) {
 #pragma unroll
     for (int i = 0; i < MI; ++i)
 #pragma unroll
@@ -238,61 +236,106 @@ __device__ __forceinline__ void row_gemm_tile(const RowGemm& g, int tm, int tn, 
   };
 
   const int nk = g.K / BK;
-  // The loads past the last step repeat its own (their lines are in L2 and
-  // nobody reads the copies): every step then has the same loads and waits, so
-  // that the compiler adds none of its own.
-  auto step = [&](auto uc, int k, auto late) __attribute__((always_inline)) {
-    constexpr int u = decltype(uc)::value;
-    using SA = std::integral_constant<int, u % 2>;
-    using NA = std::integral_constant<int, (u + 1) % 2>;
-    using SB = std::integral_constant<int, u % 3>;
-    using NB = std::integral_constant<int, (u + 2) % 3>;
-    read(SA{}, SB{}, 0);
-    issue_a(NA{}, min(k + 1, nk - 1) * BK);
-    read_done();
+  if constexpr (TL::PING) {
+    // Ping-pong K loop. Waves w and w + 4 share a SIMD; the waves of one half
+    // read fragments and issue tile loads while the other half's run MFMAs and
+    // nothing else, and a barrier swaps the roles. Step k of a wave takes four
+    // slots, two of each kind, each over half of the step's k:
+    //   M0  read the fragments of the first half; issue the loads of A for step
+    //       k+1 (its array was last read in the other half's M1 of step k-1, one
+    //       slot ago)
+    //   C0  the MFMAs
+    //   M1  read the second half; issue the loads of B for step k+2
+    //   C1  the MFMAs
+    // Waves 4-7 run one slot behind. Step k+1's tiles must have landed before
+    // waves 0-3 enter its M0: waves 0-3 wait for their loads at the end of C1,
+    // waves 4-7 at the end of M1 (the same slot); the loads of B for step k+2
+    // stay in flight. The loads past the last step repeat its own (their lines
+    // are in L2 and nobody reads the copies): every step then has the same loads
+    // and waits, so that the compiler adds none of its own.
+    auto step = [&](auto uc, int k, auto late) __attribute__((always_inline)) {
+      constexpr int u = decltype(uc)::value;
+      read(uc, 0);
+      issue_a(std::integral_constant<int, u + 1>{}, min(k + 1, nk - 1) * BK);
+      read_done();
+      barrier();
+      mfmas();
+      barrier();
+      read(uc, 1);
+      issue_b(std::integral_constant<int, u + 2>{}, min(k + 2, nk - 1) * BK);
+      read_done();
+      if constexpr (decltype(late)::value) __builtin_amdgcn_s_waitcnt(waitcnt_vm(LOADS_B));
+      barrier();
+      mfmas();
+      if constexpr (!decltype(late)::value) __builtin_amdgcn_s_waitcnt(waitcnt_vm(LOADS_B));
+      barrier();
+    };
+    // all steps of one half of the waves (a loop of its own for each half),
+    // unrolled so that every array is a compile-time choice
+    auto steps = [&](auto late) __attribute__((always_inline)) {
+      int k = 0;
+      while (true) {
+        step(Int<0>{}, k, late);
+        if (++k == nk) break;
+        step(Int<1>{}, k, late);
+        if (++k == nk) break;
+        step(Int<2>{}, k, late);
+        if (++k == nk) break;
+        step(Int<3>{}, k, late);
+        if (++k == nk) break;
+        step(Int<4>{}, k, late);
+        if (++k == nk) break;
+        step(Int<5>{}, k, late);
+        if (++k == nk) break;
+      }
+    };
+    issue_b(Int<0>{}, 0);
+    issue_a(Int<0>{}, 0);
+    issue_b(Int<1>{}, min(1, nk - 1) * BK);
+    __builtin_amdgcn_s_waitcnt(waitcnt_vm(LOADS_B));
     barrier();
-    mfmas();
-    barrier();
-    read(SA{}, SB{}, 1);
-    issue_b(NB{}, min(k + 2, nk - 1) * BK);
-    read_done();
-    if constexpr (decltype(late)::value) __builtin_amdgcn_s_waitcnt(waitcnt_vm(LOADS_B));
-    barrier();
-    mfmas();
-    if constexpr (!decltype(late)::value) __builtin_amdgcn_s_waitcnt(waitcnt_vm(LOADS_B));
-    barrier();
-  };
-  // all steps of one half of the waves (a loop of its own for each half)
-  auto steps = [&](auto late) __attribute__((always_inline)) {
+    if (__builtin_amdgcn_readfirstlane(wave) >= 4) {
+      barrier();
+      steps(std::true_type{});
+    } else {
+      steps(std::false_type{});
+      barrier();
+    }
+  } else {
+    // Ring K loop: step k's stage has landed and everyone is done with step
+    // k-1's, whose array takes the loads of step k+RING-1 (past the last step,
+    // the last step's again).
+    auto step = [&](auto uc, int k) __attribute__((always_inline)) {
+      __builtin_amdgcn_s_waitcnt(waitcnt_vm(LOADS * (RING - 2)));
+      barrier();
+      read(uc, 0);
+      using Next = Int<decltype(uc)::value + RING - 1>;
+      issue_a(Next{}, min(k + RING - 1, nk - 1) * BK);
+      issue_b(Next{}, min(k + RING - 1, nk - 1) * BK);
+      mfmas();
+      read(uc, 1);
+      mfmas();
+      read_done();
+    };
+    static_for<0, RING - 1>([&](auto uc) {
+      issue_a(uc, min(decltype(uc)::value, nk - 1) * BK);
+      issue_b(uc, min(decltype(uc)::value, nk - 1) * BK);
+    });
     int k = 0;
     while (true) {
-      step(std::integral_constant<int, 0>{}, k, late);
+      step(Int<0>{}, k);
       if (++k == nk) break;
-      step(std::integral_constant<int, 1>{}, k, late);
+      step(Int<1>{}, k);
       if (++k == nk) break;
-      step(std::integral_constant<int, 2>{}, k, late);
-      if (++k == nk) break;
-      step(std::integral_constant<int, 3>{}, k, late);
-      if (++k == nk) break;
-      step(std::integral_constant<int, 4>{}, k, late);
-      if (++k == nk) break;
-      step(std::integral_constant<int, 5>{}, k, late);
-      if (++k == nk) break;
+      if constexpr (RING > 2) {
+        step(Int<2>{}, k);
+        if (++k == nk) break;
+      }
+      if constexpr (RING > 3) {
+        step(Int<3>{}, k);
+        if (++k == nk) break;
+      }
     }
-  };
-  using S0 = std::integral_constant<int, 0>;
-  using S1 = std::integral_constant<int, 1>;
-  issue_b(S0{}, 0);
-  issue_a(S0{}, 0);
-  issue_b(S1{}, min(1, nk - 1) * BK);
-  __builtin_amdgcn_s_waitcnt(waitcnt_vm(LOADS_B));
-  barrier();
-  if (__builtin_amdgcn_readfirstlane(wave) >= 4) {
-    barrier();
-    steps(std::true_type{});
-  } else {
-    steps(std::false_type{});
-    barrier();
   }
   __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));  // the repeated loads, before the epilogue takes the arrays
 
@@ -315,11 +358,15 @@ __device__ __forceinline__ void row_gemm_tile(const RowGemm& g, int tm, int tn, 
   constexpr int QPR = TN / 4;         // 4-column groups per row
   constexpr int NT = QPR / 2;         // read-back passes of the wave per block
   constexpr int REGION = 32 * TNP * 4 + TM * (8 + 4);
-  static_assert(2 * REGION <= kTileElems * 2, "the staging of two waves must fit in an LDS array");
+  constexpr int PER = TL::PING ? 2 : (TL::WAVES + RING - 1) / RING;  // waves per array
+  static_assert(PER * REGION <= TL::ARRAY * 2 && PER * TL::ARRAYS >= TL::WAVES, "epilogue staging must fit");
   static_assert(QPR % 2 == 0, "the wave covers whole rows in each read-back pass");
   __syncthreads();  // every wave is done with the stages
-  bf16* staging = wave < 4 ? (wave < 2 ? A0 : A1) : (wave < 6 ? B0 : B1);
-  char* region = reinterpret_cast<char*>(staging) + (wave % 2) * REGION;
+  bf16* staging = lds.p[0];
+#pragma unroll
+  for (int i = 1; i < TL::ARRAYS; ++i)
+    if (wave / PER == i) staging = lds.p[i];
+  char* region = reinterpret_cast<char*>(staging) + (wave % PER) * REGION;
   float* blk = reinterpret_cast<float*>(region);
   // per block i, row r: output element offset and target (0: C, 1: C2, -1: none)
   long* row_off = reinterpret_cast<long*>(region + 32 * TNP * 4);
@@ -452,11 +499,14 @@ __device__ __forceinline__ void row_gemm_tile(const RowGemm& g, int tm, int tn, 
   }
 }
 
-// The three tilings of 8 waves (see launch_best); a 256 x 256 tile splits
-// into two 256 x 128 halves.
-using TBig = Tiling<256, 256, 64, 2, 8, 2>;
-using T192 = Tiling<256, 192, 64, 2, 8, 4>;
-using TMid = Tiling<256, 128, 64, 2, 8, 4>;
+// The tilings (see launch_best); a 256 x 256 tile splits into two 256 x 128
+// halves.
+using TBig = Tiling<256, 256, 64, 0, 8, 2>;
+using T192 = Tiling<256, 192, 64, 0, 8, 4>;
+using TMid = Tiling<256, 128, 64, 0, 8, 4>;
+using T128 = Tiling<128, 128, 64, 4, 8, 2>;
+using T64x128 = Tiling<64, 128, 64, 4, 8, 2>;
+using T64 = Tiling<64, 64, 64, 4, 4, 2>;
 
 // NOUT (1 or 3) is the number of outputs sharing A; it is a template
 // parameter so the Q/K/V projection and the output projection are distinct
@@ -472,7 +522,9 @@ template <class TL, int NOUT, int EPI, bool BUF>
 __global__ __launch_bounds__(TL::THREADS) void row_gemm_bf16_kernel(RowGemm g) {
   constexpr bool kSplit = std::is_same<TL, TBig>::value;
   static_assert(!kSplit || TMid::THREADS == TL::THREADS, "halves");
-  __shared__ __attribute__((aligned(16))) LdsTile A0, A1, B0, B1, B2;
+  __shared__ __attribute__((aligned(16))) bf16 L0[TL::ARRAY], L1[TL::ARRAY], L2[TL::ARRAYS > 2 ? TL::ARRAY : 1],
+      L3[TL::ARRAYS > 3 ? TL::ARRAY : 1], L4[TL::ARRAYS > 4 ? TL::ARRAY : 1];
+  const LdsArrays lds{{L0, L1, L2, L3, L4}};
 
   const int tiles_m = (g.M + TL::BM - 1) / TL::BM;
   const int tiles_n1 = (g.Nc + TL::BN - 1) / TL::BN;  // per output
@@ -496,26 +548,60 @@ __global__ __launch_bounds__(TL::THREADS) void row_gemm_bf16_kernel(RowGemm g) {
   const int tn = tnc - z * tiles_n1;
   if constexpr (kSplit) {
     if (half >= 0) {
-      row_gemm_tile<TMid, EPI, BUF, NOUT == 3>(g, tm, tn * 2 + half, z, A0, A1, B0, B1, B2);
+      row_gemm_tile<TMid, EPI, BUF, NOUT == 3>(g, tm, tn * 2 + half, z, lds);
       return;
     }
   }
-  row_gemm_tile<TL, EPI, BUF, NOUT == 3>(g, tm, tn, z, A0, A1, B0, B1, B2);
+  row_gemm_tile<TL, EPI, BUF, NOUT == 3>(g, tm, tn, z, lds);
 }
 
-// Rounds of a launch of `tiles` tiles on the CUs, in units of a full round
-// of this tiling: with the 256 x 256 tiling, a last round at most half full
-// is run as halves and costs a round of 256 x 128 tiles (kHalfRound).
-constexpr double kHalfRound = 0.675;
+// Cost of a launch: rounds x cost per round, in units of a full round of 256 x
+// 256 tiles (waves of 128 x 64: the fastest per FLOP). The finer grids of the
+// others fill the last round, or the only one, better. `full` is the cost of a
+// round where all CUs work, `first` what the first round costs more than that:
+// with few workgroups (or one round) each waits for its own loads and
+// barriers, and small tiles lose more to that. Measured (us, K = 8960, one
+// round of few workgroups): 131 (256 x 256), 108, 100, 58, 44, 39 (64 x 64);
+// 8190 x 5120 x 5120, per full round: 112, 84, 70, 41, 29, and 32 for two
+// workgroups of 64 x 64 per CU.
+template <class TL>
+struct Cost;
+template <>
+struct Cost<TBig> { static constexpr double full = 1.0, first = 0.0; static constexpr int per_cu = 1; };
+template <>
+struct Cost<T192> { static constexpr double full = 0.78, first = 0.04; static constexpr int per_cu = 1; };
+template <>
+struct Cost<TMid> { static constexpr double full = 0.64, first = 0.12; static constexpr int per_cu = 1; };
+template <>
+struct Cost<T128> { static constexpr double full = 0.38, first = 0.06; static constexpr int per_cu = 1; };
+template <>
+struct Cost<T64x128> { static constexpr double full = 0.26, first = 0.075; static constexpr int per_cu = 1; };
+template <>
+struct Cost<T64> { static constexpr double full = 0.30, first = 0.09; static constexpr int per_cu = 2; };
+
+// With the 256 x 256 tiling, a last round at most half full is run as halves
+// and costs a round of 256 x 128 tiles.
 template <class TL>
 bool split_tail(long tiles) {
   const long cus = compute_units(), rem = tiles % cus;
   return std::is_same<TL, TBig>::value && tiles > cus && rem > 0 && 2 * rem <= cus;
 }
 template <class TL>
-double rounds(long tiles) {
-  const long cus = compute_units();
-  return split_tail<TL>(tiles) ? (double)(tiles / cus) + kHalfRound : (double)((tiles + cus - 1) / cus);
+double estimate(const RowGemm& g) {
+  typedef Cost<TL> C;
+  const long tiles = (long)((g.M + TL::BM - 1) / TL::BM) * ((g.Nc + TL::BN - 1) / TL::BN) * g.n_out;
+  const long cus = compute_units(), slots = cus * C::per_cu;
+  if (split_tail<TL>(tiles)) return (double)(tiles / cus) + Cost<TMid>::full;
+  // a CU with one workgroup where two fit: measured as if the round were full,
+  // without what the first costs more
+  if (C::per_cu > 1 && tiles <= cus) return C::full;
+  return (double)((tiles + slots - 1) / slots) * C::full + C::first;
+}
+
+// buffer resources address 4 GiB - 1 bytes from their base (32-bit offsets)
+bool buffer_sized(const RowGemm& g) {
+  const long lim = 0xffffffffL;
+  return (long)g.a_limit * g.lda * 2 <= lim && (long)g.Nc * g.ldb * 2 <= lim;
 }
 
 template <class TL, int NOUT, int EPI>
@@ -532,48 +618,42 @@ hipError_t launch(const RowGemm& g0, hipStream_t s) {
     g.split_from = (int)(tiles - rem);
     grid = tiles + rem;
   }
-  // buffer resources address 4 GiB - 1 bytes from their base (32-bit offsets)
-  const long lim = 0xffffffffL;
-  if ((long)g.a_limit * g.lda * 2 <= lim && (long)g.Nc * g.ldb * 2 <= lim)
-    hipLaunchKernelGGL((row_gemm_bf16_kernel<TL, NOUT, EPI, true>), dim3((unsigned)grid), dim3(TL::THREADS), 0, s, g);
-  else
-    hipLaunchKernelGGL((row_gemm_bf16_kernel<TL, NOUT, EPI, false>), dim3((unsigned)grid), dim3(TL::THREADS), 0, s, g);
+  if constexpr (TL::PING) {
+    if (!buffer_sized(g)) {
+      hipLaunchKernelGGL((row_gemm_bf16_kernel<TL, NOUT, EPI, false>), dim3((unsigned)grid), dim3(TL::THREADS), 0, s, g);
+      return hipGetLastError();
+    }
+  }
+  hipLaunchKernelGGL((row_gemm_bf16_kernel<TL, NOUT, EPI, true>), dim3((unsigned)grid), dim3(TL::THREADS), 0, s, g);
   return hipGetLastError();
 }
 
-// Three tilings of 8 waves. Per FLOP 256 x 256 (waves of 128 x 64) is the
-// fastest; 256 x 192 (waves of 64 x 96) costs about 1.14x and 256 x 128
-// (waves of 64 x 64) about 1.35x (measured on the stack shapes), but their
-// finer grids can fill the last round of a launch better. Each launch takes
-// the tiling with the least estimated time, rounds x cost per round, with
-// rounds as counted by rounds() (ceil(tiles / CUs), or the split tail of
-// 256 x 256) and the per-round cost relative to 256 x 256 (tile area x cost
-// per FLOP): 1, 0.855, 0.675. A tiling other than 256 x 256 must win by 3%.
-// The narrow fp32 velocity head always takes 256 x 128.
-template <class TL>
-double estimate(const RowGemm& g, double per_round) {
-  const long tiles = (long)((g.M + TL::BM - 1) / TL::BM) * ((g.Nc + TL::BN - 1) / TL::BN) * g.n_out;
-  return rounds<TL>(tiles) * per_round;
-}
-
+// The tiling of least estimated cost; a smaller one must win by 2%. Matrices
+// of 4 GiB or more take one of the large three (the others have no 64-bit
+// loads: such a product has rows or columns for many large tiles).
 template <int NOUT, int EPI>
 hipError_t launch_best(const RowGemm& g, hipStream_t s) {
-  const double eb = estimate<TBig>(g, 1.0), e192 = estimate<T192>(g, 0.855),
-               em = estimate<TMid>(g, kHalfRound);
-  if (e192 < 0.97 * eb && e192 <= em) return launch<T192, NOUT, EPI>(g, s);
-  if (em < 0.97 * eb && em < e192) return launch<TMid, NOUT, EPI>(g, s);
-  return launch<TBig, NOUT, EPI>(g, s);
+  typedef hipError_t (*Launch)(const RowGemm&, hipStream_t);
+  const double cost[] = {estimate<TBig>(g), estimate<T192>(g),    estimate<TMid>(g),
+                         estimate<T128>(g), estimate<T64x128>(g), estimate<T64>(g)};
+  static constexpr Launch with[] = {launch<TBig, NOUT, EPI>, launch<T192, NOUT, EPI>,    launch<TMid, NOUT, EPI>,
+                                    launch<T128, NOUT, EPI>, launch<T64x128, NOUT, EPI>, launch<T64, NOUT, EPI>};
+  int best = 0;
+  const int n = buffer_sized(g) ? 6 : 3;
+  for (int i = 1; i < n; ++i)
+    if (cost[i] < 0.98 * cost[best]) best = i;
+  return with[best](g, s);
 }
 
 }  // namespace
 
 hipError_t launch_row_gemm_bf16(const RowGemm& g, hipStream_t s) {
   if (g.M <= 0 || g.Nc <= 0 || (g.n_out != 1 && g.n_out != 3)) return hipSuccess;
-  if (g.K % TBig::BK || g.K % T192::BK || g.K % TMid::BK) return hipErrorInvalidValue;
+  if (g.K % TBig::BK) return hipErrorInvalidValue;
   if (g.rope_cs && g.rope_outs && g.n_out != 3) return hipErrorInvalidValue;  // RoPE: Q/K/V only
   if (g.residual && g.out[0].c_limit <= 0) return hipSuccess;  // no output row
   if (g.n_out == 3) return launch_best<3, kEpiBf16>(g, s);
-  if (g.c_f32) return launch<TMid, 1, kEpiF32>(g, s);
+  if (g.c_f32) return launch_best<1, kEpiF32>(g, s);
   if (g.gelu) return launch_best<1, kEpiBf16Gelu>(g, s);
   if (g.residual) return launch_best<1, kEpiBf16Residual>(g, s);
   return launch_best<1, kEpiBf16>(g, s);

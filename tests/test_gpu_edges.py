@@ -168,3 +168,50 @@ def test_l1_rel_edges(n, channels):
     tp.zero_()
     H.hsa_l1_rel_accumulate(tv, tp, ta, True)
     assert torch.count_nonzero(ta) == 0 and torch.equal(tp, tv)
+
+
+# one shape per tiling of the bf16 product on 256 compute units (64 x 64, 64 x 128, 128 x 128, 256 x 128,
+# 256 x 192, 256 x 256, 256 x 256 with a split last round), all with ragged last rows and columns
+GEMM_SHAPES = [(65, 68), (1000, 1532), (2000, 1532), (4090, 1532), (8190, 1532), (2590, 5116), (8190, 5116)]
+
+
+# K steps 1 .. 8: the ends of the loops unrolled by 4 and 6
+@pytest.mark.parametrize("m,n", GEMM_SHAPES)
+@pytest.mark.parametrize("steps", [1, 2, 3, 4, 5, 6, 7, 8])
+def test_linear_bf16_edges(m, n, steps):
+    g = torch.Generator(device=DEV).manual_seed(m + n + steps)
+    k = 64 * steps
+    x = torch.randn(m, k, generator=g, device=DEV).to(torch.bfloat16)
+    w = (torch.randn(n, k, generator=g, device=DEV) * k ** -0.5).to(torch.bfloat16)
+    r = torch.randn(m, n, generator=g, device=DEV).to(torch.bfloat16)
+    y = torch.full((m + 1, n), 7.0, device=DEV, dtype=torch.bfloat16)
+    H.hsa_linear(x, m, w, y, residual=r)
+    want = x.float() @ w.float().t() + r.float()
+    # one rounding to bf16 of a value that carries a few fp32 ulps of its terms
+    err = (y[:m].float() - want).abs()
+    assert bool((err <= 2.0 ** -8 * want.abs() + 1e-5).all())
+    assert bool((y[m] == 7.0).all())
+    f = torch.full((m + 1, n), 7.0, device=DEV)
+    H.hsa_linear(x, m, w, f)
+    assert float((f[:m] - (want - r.float())).abs().max()) < 1e-4
+    assert bool((f[m] == 7.0).all())
+
+
+@pytest.mark.parametrize("m,d", [(70, 64), (300, 256), (700, 1536), (2000, 1536)])
+def test_qkv_bf16_small_tilings_scatter(m, d):
+    """Gathered rows in, scattered rows out, on the small tilings; other cache rows untouched."""
+    g = torch.Generator(device=DEV).manual_seed(m + d)
+    n = 2 * m + 5
+    x = torch.randn(n, d, generator=g, device=DEV).to(torch.bfloat16)
+    ws = [(torch.randn(d, d, generator=g, device=DEV) * d ** -0.5).to(torch.bfloat16) for _ in range(3)]
+    idx = torch.sort(torch.randperm(n, generator=g, device=DEV)[:m]).values.to(torch.int32)
+    q = torch.empty(m, d, device=DEV, dtype=torch.bfloat16)
+    kc, vc = (torch.full((n, d), 7.0, device=DEV, dtype=torch.bfloat16) for _ in range(2))
+    H.hsa_qkv_scatter(x, idx, m, *ws, q, kc, vc)
+    rows = x[idx.long()].float()
+    for out, w in ((q, ws[0]), (kc[idx.long()], ws[1]), (vc[idx.long()], ws[2])):
+        want = rows @ w.float().t()
+        assert bool(((out.float() - want).abs() <= 2.0 ** -8 * want.abs() + 1e-5).all())
+    skipped = torch.ones(n, dtype=torch.bool, device=DEV)
+    skipped[idx.long()] = False
+    assert bool((kc[skipped] == 7.0).all()) and bool((vc[skipped] == 7.0).all())
