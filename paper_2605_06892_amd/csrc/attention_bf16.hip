@@ -446,6 +446,204 @@ __global__ __launch_bounds__(256) void attention_combine_kernel(const float* __r
   }
 }
 
+// Small launches: 16 queries of one head per workgroup, whose 8 waves split the
+// cached rows (wave w takes the 32-key blocks w, w+8, ...) and merge their
+// softmaxes in LDS. The main kernel walks all rows of a part in one chain of
+// blocks, 0.85 us each, however few workgroups there are; here the chain is an
+// eighth of it and the grid has 16 times the workgroups, at 16 times the loads
+// per product: launch_attention_bf16 says where the line lies.
+//
+// Per 32-key block of a wave: S^T = K Q^T by v_mfma_f32_16x16x32_bf16, K rows
+// straight from global memory in the A operand's layout (lane: key l16, channels
+// grp*8 ..); each lane holds 8 scores of ONE query (keys kt*16 + grp*4 + e),
+// which are the B operand of O^T += V^T P^T as they sit (slot grp*8 + kt*4 + e).
+// V rows go through the wave's LDS region for the transpose read. Both are
+// loaded one block ahead.
+constexpr int kSmallWaves = 8, kSmallQ = 16;
+
+template <int DH, bool SPLIT>
+__global__ __launch_bounds__(kSmallWaves * 64) void attention_small_kernel(
+    const bf16* __restrict__ q, const bf16* __restrict__ kc, const bf16* __restrict__ vc,
+    bf16* __restrict__ o, int n_q, int n_kv, int d, float sl2e, int n_qtiles,
+    const bf16* __restrict__ kc2, const bf16* __restrict__ vc2, int n_split) {
+  constexpr int KK = DH / 32;              // k-steps of S^T
+  constexpr int DT = DH / 16;              // 16-wide head-dim tiles of O^T
+  constexpr int CPR = DH / 8;              // 16-byte chunks per row
+  constexpr int LV = 32 * CPR / 64;        // V loads per lane and block
+  constexpr int P = DH + 4;                // padded row of the merge buffer, floats
+  __shared__ __attribute__((aligned(16))) float buf[kSmallWaves][kSmallQ * P];  // V rows, then the merge
+  __shared__ float m_part[kSmallWaves][kSmallQ], l_part[kSmallWaves][kSmallQ];
+  static_assert(kSmallQ * P * 4 >= 32 * DH * 2, "a block's V rows fit");
+  const int heads = d / DH;
+  const int item = xcd_contiguous(blockIdx.x, n_qtiles * heads);
+  const int h = item / n_qtiles, qt = item - h * n_qtiles;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int l16 = lane & 15, grp = lane >> 4;
+  const long col0 = (long)h * DH;
+
+  // row n of the keys or values (rows past n_kv repeat the last one, masked below)
+  auto row = [&](const bf16* a, const bf16* a2, int n) -> const bf16* {
+    n = min(n, n_kv - 1);
+    if (SPLIT && n >= n_split) return a2 + (long)(n - n_split) * d + col0;
+    return a + (long)n * d + col0;
+  };
+  bf16x8 kf[2][KK], vr[LV];
+  auto load = [&](int n0) {
+    if (n0 >= n_kv) return;
+#pragma unroll
+    for (int kt = 0; kt < 2; ++kt) {
+      const bf16* kr = row(kc, kc2, n0 + kt * 16 + l16) + grp * 8;
+#pragma unroll
+      for (int kk = 0; kk < KK; ++kk) kf[kt][kk] = *reinterpret_cast<const bf16x8*>(kr + kk * 32);
+    }
+#pragma unroll
+    for (int i = 0; i < LV; ++i) {
+      const int f = i * 64 + lane;
+      vr[i] = *reinterpret_cast<const bf16x8*>(row(vc, vc2, n0 + f / CPR) + f % CPR * 8);
+    }
+  };
+  load(wave * 32);
+
+  // Q, pre-scaled by scale*log2(e) (rows past n_q repeat the last one and are not stored)
+  bf16x8 qf[KK];
+  {
+    const bf16* qr = q + (long)min(qt * kSmallQ + l16, n_q - 1) * d + col0 + grp * 8;
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) {
+      const bf16x8 raw = *reinterpret_cast<const bf16x8*>(qr + kk * 32);
+      f32x4 lo = {(float)raw[0] * sl2e, (float)raw[1] * sl2e, (float)raw[2] * sl2e, (float)raw[3] * sl2e};
+      f32x4 up = {(float)raw[4] * sl2e, (float)raw[5] * sl2e, (float)raw[6] * sl2e, (float)raw[7] * sl2e};
+      qf[kk] = __builtin_shufflevector(to_bf16x4(lo), to_bf16x4(up), 0, 1, 2, 3, 4, 5, 6, 7);
+    }
+  }
+
+  // V rows in LDS: chunk c of row r at slot c ^ f(r), so that the rows' writes
+  // and the transpose reads (16 rows, 2 chunks) hit disjoint banks
+  bf16* vl = reinterpret_cast<bf16*>(buf[wave]);
+  auto swz = [](int r) { return DH == 128 ? (r & 7) << 1 : ((r >> 1) & 3) << 1; };
+  f32x4 acc[DT];
+#pragma unroll
+  for (int dt = 0; dt < DT; ++dt) acc[dt] = (f32x4){};
+  float m_run = -INFINITY, l_run = 0.f;
+  for (int n0 = wave * 32; n0 < n_kv; n0 += kSmallWaves * 32) {
+#pragma unroll
+    for (int i = 0; i < LV; ++i) {
+      const int f = i * 64 + lane, r = f / CPR;
+      *reinterpret_cast<bf16x8*>(vl + r * DH + ((f % CPR) ^ swz(r)) * 8) = vr[i];
+    }
+    f32x4 s[2] = {};
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk)
+#pragma unroll
+      for (int kt = 0; kt < 2; ++kt)
+        s[kt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[kt][kk], qf[kk], s[kt], 0, 0, 0);
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");  // the V rows are in LDS
+    load(n0 + kSmallWaves * 32);
+    if (n0 + 32 > n_kv) {
+#pragma unroll
+      for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (n0 + kt * 16 + grp * 4 + e >= n_kv) s[kt][e] = -INFINITY;
+    }
+    float mx = fmaxf(fmaxf(fmaxf(s[0][0], s[0][1]), fmaxf(s[0][2], s[0][3])),
+                     fmaxf(fmaxf(s[1][0], s[1][1]), fmaxf(s[1][2], s[1][3])));
+    mx = fmaxf(mx, __shfl_xor(mx, 16));
+    mx = fmaxf(mx, __shfl_xor(mx, 32));
+    if (__any(mx > m_run)) {
+      const float m_new = fmaxf(m_run, mx);
+      const float alpha = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run - m_new);
+      l_run *= alpha;
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt) acc[dt] *= alpha;
+      m_run = m_new;
+    }
+    const float m_use = m_run == -INFINITY ? 0.f : m_run;  // only -inf scores so far: weights 0
+    f32x4 p[2];
+#pragma unroll
+    for (int kt = 0; kt < 2; ++kt)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        p[kt][e] = __builtin_amdgcn_exp2f(s[kt][e] - m_use);
+        l_run += p[kt][e];
+      }
+    const bf16x8 pf = __builtin_shufflevector(to_bf16x4(p[0]), to_bf16x4(p[1]), 0, 1, 2, 3, 4, 5, 6, 7);
+    const int r = grp * 4 + (l16 >> 2);  // this lane's row of the transpose reads (+ 16)
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) {
+      const int col = dt * 16 + 4 * (lane & 3);
+      const bf16* src = vl + r * DH + (((col >> 3) ^ swz(r)) * 8) + (col & 7);
+      const bf16x4 v0 = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(src));
+      const bf16x4 v1 = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)(src + 16 * DH));
+      acc[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_shufflevector(v0, v1, 0, 1, 2, 3, 4, 5, 6, 7), pf,
+                                                        acc[dt], 0, 0, 0);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");  // read before the next block's rows
+  }
+
+  // merge: the waves' softmaxes, each rescaled to the common maximum.
+  // acc[dt][e]: channel dt*16 + grp*4 + e of query l16
+  float l_tot = l_run + __shfl_xor(l_run, 16);
+  l_tot += __shfl_xor(l_tot, 32);
+  if (grp == 0) {
+    m_part[wave][l16] = m_run;
+    l_part[wave][l16] = l_tot;
+  }
+#pragma unroll
+  for (int dt = 0; dt < DT; ++dt)
+    *reinterpret_cast<f32x4*>(&buf[wave][l16 * P + dt * 16 + grp * 4]) = acc[dt];
+  __syncthreads();
+  for (int f = threadIdx.x; f < kSmallQ * DH / 4; f += kSmallWaves * 64) {
+    const int r = f / (DH / 4), c = (f - r * (DH / 4)) * 4;
+    const int qrow = qt * kSmallQ + r;
+    if (qrow >= n_q) continue;
+    float m = -INFINITY;
+#pragma unroll
+    for (int w = 0; w < kSmallWaves; ++w) m = fmaxf(m, m_part[w][r]);
+    f32x4 sum = {};
+    float l = 0.f;
+#pragma unroll
+    for (int w = 0; w < kSmallWaves; ++w) {
+      const float mw = m_part[w][r];
+      const float wt = mw == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mw - m);  // 0: no finite score, or no key
+      l = fmaf(wt, l_part[w][r], l);
+      sum += wt * *reinterpret_cast<const f32x4*>(&buf[w][r * P + c]);
+    }
+    *reinterpret_cast<bf16x4*>(o + (long)qrow * d + col0 + c) = to_bf16x4(sum * (1.f / l));
+  }
+}
+
+// Estimated times (us, MI355X): the main kernel takes 9 and 0.57 per 32-key
+// block of 128-wide heads for each round of its workgroups on the CUs, and 4 to
+// merge key parts, the small one 4.5 and 0.26. Measured, main against
+// small: 500 queries and 1000 rows of 2 heads 27.1 and 12.9, 80 x 500 x 8 heads
+// 15.0 and 8.8, 300 x 1600 x 8 28.6 and 18.1, 400 x 512 x 12 18.6 and 16.4; but 800 x
+// 512 x 12 18.9 and 24.1, 1000 x 4000 x 12 42 and 117.
+bool small_is_faster(int n_q, int n_kv, int heads, int head_dim, long main_wgs, int parts) {
+  const long cus = compute_units(), wgs = (long)((n_q + kSmallQ - 1) / kSmallQ) * heads;
+  const double blocks = (double)((n_kv + 31L) / 32) * head_dim / 128;
+  const double main_us = (double)((main_wgs * parts + cus - 1) / cus) * (9.0 + 0.57 * blocks / parts) +
+                         (parts > 1 ? 4.0 : 0.0);
+  const double small_us = (double)((wgs + cus - 1) / cus) * (4.5 + 0.26 * blocks);
+  return small_us < 0.9 * main_us;
+}
+
+template <int DH>
+hipError_t launch_small(const void* q, const void* k, const void* v, void* o, int n_q, int n_kv, int heads,
+                        float sl2e, hipStream_t s, const void* k2, const void* v2, int n_split) {
+  const int n_qtiles = (n_q + kSmallQ - 1) / kSmallQ;
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)((long)n_qtiles * heads)), dim3(kSmallWaves * 64), 0, s,
+                       static_cast<const bf16*>(q), static_cast<const bf16*>(k), static_cast<const bf16*>(v),
+                       static_cast<bf16*>(o), n_q, n_kv, heads * DH, sl2e, n_qtiles,
+                       static_cast<const bf16*>(k2), static_cast<const bf16*>(v2), n_split);
+  };
+  if (n_split < n_kv) launch(attention_small_kernel<DH, true>);
+  else launch(attention_small_kernel<DH, false>);
+  return hipGetLastError();
+}
+
 template <int DH, int NW, bool SPLIT>
 hipError_t launch_split(const void* q, const void* k, const void* v, void* o, int n_q, int n_kv,
                         int heads, float sl2e, hipStream_t s, const void* k2, const void* v2,
@@ -540,6 +738,9 @@ hipError_t launch_attention_bf16(const void* q, const void* k, const void* v, vo
   const int nw = (forced && atoi(forced) == 4) ? 4 : 8;
   const int wgs = (n_q + nw * 32 - 1) / (nw * 32) * heads;
   const KvParts kp = choose_kv_parts(wgs, n_q, n_kv, heads, head_dim, ws, ws_bytes);
+  if (!forced && !getenv("HSA_ATTN_KV_PARTS") && small_is_faster(n_q, n_kv, heads, head_dim, wgs, kp.parts))
+    return head_dim == 64 ? launch_small<64>(q, k, v, o, n_q, n_kv, heads, sl2e, s, k2, v2, n_split)
+                          : launch_small<128>(q, k, v, o, n_q, n_kv, heads, sl2e, s, k2, v2, n_split);
   if (head_dim == 64)
     return nw == 8 ? launch_cfg<64, 8>(q, k, v, o, n_q, n_kv, heads, sl2e, s, k2, v2, n_split, kp)
                    : launch_cfg<64, 4>(q, k, v, o, n_q, n_kv, heads, sl2e, s, k2, v2, n_split, kp);

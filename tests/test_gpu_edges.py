@@ -215,3 +215,30 @@ def test_qkv_bf16_small_tilings_scatter(m, d):
     skipped = torch.ones(n, dtype=torch.bool, device=DEV)
     skipped[idx.long()] = False
     assert bool((kc[skipped] == 7.0).all()) and bool((vc[skipped] == 7.0).all())
+
+
+# queries around the 16-query tiles of a wave and the 256 of a workgroup, rows around the 16-key tiles,
+# the 32-key blocks and the 96-row LDS tiles
+@pytest.mark.parametrize("n_q,n_kv,heads,dh", [
+    (1, 1, 1, 128), (15, 15, 2, 64), (16, 17, 2, 128), (17, 31, 1, 128), (33, 95, 2, 128), (255, 97, 1, 64),
+    (257, 193, 3, 128), (300, 400, 2, 64), (500, 1000, 2, 128), (40, 3000, 1, 128), (700, 77, 12, 128),
+])
+@pytest.mark.parametrize("spread", [1.0, 12.0])
+def test_attention_bf16_edges(n_q, n_kv, heads, dh, spread):
+    """With and without a scratch for key parts; spread 12: the reference maximum has to be raised."""
+    g = _gen(n_q * 1000 + n_kv)
+    d = heads * dh
+    q, k, v = ((torch.randn(n, d, generator=g) * s).to(torch.bfloat16)
+               for n, s in ((n_q, spread), (n_kv, 1.0), (n_kv, 1.0)))
+    want = _attend64(q, k, v, heads)
+    tq, tk, tv = (t.to(DEV) for t in (q, k, v))
+    parts = torch.empty(4 * n_q * heads * (dh + 2) * 4, dtype=torch.uint8, device=DEV)
+    # q rescaled and rounded to bf16 moves a score s by up to 2^-8 |s|, which is its probability's
+    # relative error (random signs over dh products: a few sigma of s 2^-9 / sqrt(dh) each); p and o
+    # round once each
+    bar = 2.0 ** -7 * (1 + 0.5 * spread)
+    for scratch in (None, parts):
+        out = torch.full((n_q + 1, d), 7.0, device=DEV, dtype=torch.bfloat16)
+        H.hsa_attention_core(tq, tk, tv, n_q, heads, dh, dh ** -0.5, out, parts=scratch)
+        assert float((out[:n_q].cpu().double() - want).abs().max() / want.abs().max()) < bar
+        assert bool((out[n_q] == 7.0).all())
