@@ -74,7 +74,8 @@ __global__ __launch_bounds__(kThreads) void active_set_kernel(const int32_t* __r
                                                               int n, int range, int T, int iter,
                                                               int margin, int outside_period,
                                                               int32_t* __restrict__ idx,
-                                                              int32_t* __restrict__ n_active) {
+                                                              int32_t* __restrict__ n_active,
+                                                              int32_t* n_active_host) {
   __shared__ int wave_total[kThreads / kWave];
   __shared__ unsigned char table[kMaxTableT + 1];
 
@@ -198,14 +199,20 @@ __global__ __launch_bounds__(kThreads) void active_set_kernel(const int32_t* __r
   }
   if (blockIdx.x == gridDim.x - 1) {  // this workgroup has seen every token
     const int any_bad = block_sum(bad, wave_total);
-    if (t == 0) n_active[0] = any_bad ? -1 : base;
+    if (t == 0) {
+      const int count = any_bad ? -1 : base;
+      n_active[0] = count;
+      // pinned host memory: the host reads it after synchronizing the stream
+      if (n_active_host) __hip_atomic_store(n_active_host, count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
   }
 }
 
 }  // namespace
 
 hipError_t launch_active_set(const int32_t* budget, int n, int T, int iter, int margin,
-                             int outside_period, int32_t* idx, int32_t* n_active, hipStream_t s) {
+                             int outside_period, int32_t* idx, int32_t* n_active, hipStream_t s,
+                             int32_t* n_active_host) {
   // up to 16 ranges of at least 4096 tokens (a multiple of 4 each)
   constexpr int kMaxGroups = 16, kMinRange = 4096;
   int groups = (int)std::min<long>(kMaxGroups, std::max<long>(1, ((long)n + kMinRange - 1) / kMinRange));
@@ -213,7 +220,7 @@ hipError_t launch_active_set(const int32_t* budget, int n, int T, int iter, int 
   if (range < 4) range = 4;
   groups = (int)std::max<long>(1, ((long)n + range - 1) / range);
   hipLaunchKernelGGL(active_set_kernel, dim3(groups), dim3(kThreads), 0, s, budget, n, range, T, iter,
-                     margin, outside_period, idx, n_active);
+                     margin, outside_period, idx, n_active, n_active_host);
   return hipGetLastError();
 }
 

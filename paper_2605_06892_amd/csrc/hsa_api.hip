@@ -26,6 +26,21 @@ HSA_API int32_t hsa_window_margin(int32_t center_percent, int32_t T) {
   return (int32_t)(((int64_t)(100 - center_percent) * T) / 200);
 }
 
+namespace {
+
+// The device's address of an int32 in pinned host memory (of the current
+// device's context), or NULL for any other memory.
+int32_t* device_view(int32_t* host) {
+  hipPointerAttribute_t attr{};
+  if (hipPointerGetAttributes(&attr, host) != hipSuccess) {
+    (void)hipGetLastError();  // pageable memory: not an error of this call
+    return nullptr;
+  }
+  return attr.type == hipMemoryTypeHost ? static_cast<int32_t*>(attr.devicePointer) : nullptr;
+}
+
+}  // namespace
+
 HSA_API int hsa_build_active_set_window(const int32_t* budget, int64_t n_tokens, int32_t T,
                                         int32_t iter, int32_t margin, int32_t outside_period,
                                         int32_t* idx, int32_t* n_active_dev,
@@ -38,13 +53,15 @@ HSA_API int hsa_build_active_set_window(const int32_t* budget, int64_t n_tokens,
   if (overlaps(idx, nb, budget, nb) || overlaps(n_active_dev, 4, budget, nb) ||
       overlaps(n_active_dev, 4, idx, nb))
     return HSA_STEP_ERR_ALIAS;
+  // Into pinned host memory the kernel writes the count itself; a copy behind it
+  // is a launch of its own (27.4 against 25.9 us for the whole call at 32760 tokens).
+  int32_t* host_dev = n_active_host ? device_view(n_active_host) : nullptr;
   hipError_t e = hsa::launch_active_set(budget, (int)n_tokens, T, iter, margin, outside_period, idx,
-                                        n_active_dev, stream);
+                                        n_active_dev, stream, host_dev);
   if (e != hipSuccess) return HSA_STEP_ERR_LAUNCH;
   if (n_active_host) {
-    // straight into the caller's int: a direct DMA when it is pinned host memory
-    if (hipMemcpyAsync(n_active_host, n_active_dev, sizeof(int32_t), hipMemcpyDeviceToHost, stream) !=
-            hipSuccess ||
+    if ((!host_dev && hipMemcpyAsync(n_active_host, n_active_dev, sizeof(int32_t), hipMemcpyDeviceToHost,
+                                     stream) != hipSuccess) ||
         hipStreamSynchronize(stream) != hipSuccess)
       return HSA_STEP_ERR_LAUNCH;
     if (*n_active_host < 0) return HSA_STEP_ERR_BUDGET;

@@ -188,7 +188,7 @@ def hsa_build_active_set(budget, T: int, iteration: int, margin: int, idx, n_act
     """Fill idx[:|A_i|] with the active set; returns |A_i| when read_back
     (one stream synchronization), else None. outside_period != 1 calls
     hsa_build_active_set_window. host_buf: optional pinned int32 CPU tensor
-    of one element that receives the count (a direct DMA)."""
+    of one element that receives the count (written by the kernel)."""
     _dev(budget, idx, n_active_dev)
     host = ctypes.c_int32(-2)
     if host_buf is not None:
