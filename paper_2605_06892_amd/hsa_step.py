@@ -142,26 +142,34 @@ class HsaStack(ctypes.Structure):
     ]
 
 
+# The short calls are bound by this marshalling (an Euler update of 75600 x 16 is 6.6 us of kernel):
+# plain integers, which ctypes converts itself, and the current stream's handle without its
+# Python object.
+
+
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream(stream):
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return stream.cuda_stream
+
+
+_DTYPES = {torch.bfloat16: BF16, torch.float32: F32}
 
 
 def _dtype(*ts) -> int:
-    dts = {t.dtype for t in ts if t is not None}
-    if len(dts) != 1:
-        raise TypeError(f"tensors must share one dtype, got {dts}")
-    dt = dts.pop()
-    if dt == torch.bfloat16:
-        return BF16
-    if dt == torch.float32:
-        return F32
-    raise TypeError(f"unsupported dtype {dt}")
+    dt = None
+    for t in ts:
+        if t is not None and t.dtype != dt:
+            if dt is not None:
+                raise TypeError(f"tensors must share one dtype, got {dt} and {t.dtype}")
+            dt = t.dtype
+    if dt not in _DTYPES:
+        raise TypeError(f"unsupported dtype {dt}")
+    return _DTYPES[dt]
 
 
 def _check(fn: str, st: int) -> None:
