@@ -9,6 +9,7 @@ namespace hsa {
 typedef __bf16 bf16;
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));  // 16 raw bytes
@@ -116,6 +117,10 @@ struct RowGemm {
   const int32_t* rope_tok;
   const int32_t* rope_pos;
   int rope_outs, rope_dh, rope_nt, rope_nh, rope_f, rope_h, rope_w;
+  // set by the bf16 launcher: each product row is scaled by 1 / sqrt(mean of
+  // its A row's squares + rms_eps), formed in the kernel (small tilings only)
+  int rms;
+  float rms_eps;
   // set by the bf16 launcher: workgroups from this index on take halves of
   // the remaining 256x256 tiles (see gemm_bf16.hip)
   int split_from;
@@ -151,6 +156,10 @@ __device__ __forceinline__ f32x2 rope_pair(const RowGemm& g, const RopeRow& r, i
   return rope_rotate(rope_angle(g, r, k), a, b);
 }
 hipError_t launch_row_gemm_bf16(const RowGemm& g, hipStream_t s);
+// The product with its rows scaled by 1 / sqrt(mean of the A row's squares +
+// eps); A is compact (no a_rows, lda = K, M rows). The factors are formed inside the
+// small tilings' kernel, else by launch_row_rms_scale into scale[M].
+hipError_t launch_rms_row_gemm_bf16(const RowGemm& g, float eps, float* scale, hipStream_t s);
 
 // Output z of a RowGemm, selected field by field so that a kernel never
 // indexes its by-value argument dynamically (which would copy it to scratch).

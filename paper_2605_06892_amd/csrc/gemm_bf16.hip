@@ -236,6 +236,9 @@ __device__ __forceinline__ void row_gemm_tile(const RowGemm& g, int tm, int tn, 
   };
 
   const int nk = g.K / BK;
+  float sq[MI];  // ring, g.rms: sums of squares of the lane's A rows
+#pragma unroll
+  for (int i = 0; i < MI; ++i) sq[i] = 0.f;
   if constexpr (TL::PING) {
     // Ping-pong K loop. Waves w and w + 4 share a SIMD; the waves of one half
     // read fragments and issue tile loads while the other half's run MFMAs and
@@ -305,6 +308,20 @@ __device__ __forceinline__ void row_gemm_tile(const RowGemm& g, int tm, int tn, 
     // Ring K loop: step k's stage has landed and everyone is done with step
     // k-1's, whose array takes the loads of step k+RING-1 (past the last step,
     // the last step's again).
+    // With g.rms a wave also sums the squares of its A rows, 8 channels of
+    // row l16 of each row tile per fragment (a launch of few tiles waits for its
+    // chain of steps, not for these; a kernel of its own for them costs 4 us:
+    // an iteration of three blocks, 500 rows at d = 256, 241 -> 220 us).
+    auto squares = [&]() __attribute__((always_inline)) {
+      if (!g.rms) return;
+#pragma unroll
+      for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const bf16x2 pair = {af[i][2 * u], af[i][2 * u + 1]};
+          sq[i] = __builtin_amdgcn_fdot2_f32_bf16(pair, pair, sq[i], false);
+        }
+    };
     auto step = [&](auto uc, int k) __attribute__((always_inline)) {
       __builtin_amdgcn_s_waitcnt(waitcnt_vm(LOADS * (RING - 2)));
       barrier();
@@ -313,8 +330,10 @@ __device__ __forceinline__ void row_gemm_tile(const RowGemm& g, int tm, int tn, 
       issue_a(Next{}, min(k + RING - 1, nk - 1) * BK);
       issue_b(Next{}, min(k + RING - 1, nk - 1) * BK);
       mfmas();
+      squares();
       read(uc, 1);
       mfmas();
+      squares();
       read_done();
     };
     static_for<0, RING - 1>([&](auto uc) {
@@ -389,6 +408,13 @@ __device__ __forceinline__ void row_gemm_tile(const RowGemm& g, int tm, int tn, 
     const int cr = c_rows ? c_rows[mc] : m;
     crow[i] = m < g.M ? cr : -1;
     rs[i] = g.row_scale ? g.row_scale[mc] : 1.f;
+    if constexpr (!TL::PING) {
+      if (g.rms) {
+        float t = sq[i] + __shfl_xor(sq[i], 16);
+        t += __shfl_xor(t, 32);
+        rs[i] = 1.0f / sqrtf(t / (float)g.K + g.rms_eps);
+      }
+    }
     rr[i] = RopeRow{0, 0, 0};
     if (rope) rr[i] = rope_row(g, mc);
   }
@@ -450,7 +476,7 @@ __device__ __forceinline__ void row_gemm_tile(const RowGemm& g, int tm, int tn, 
 #pragma unroll
       for (int j = 0; j < NI; ++j) {
         f32x4 v = acc[it][j];
-        if (g.row_scale) v *= rs[it];
+        if (g.row_scale || (!TL::PING && g.rms)) v *= rs[it];
         if (rope) {
           const f32x2 r0 = rope_rotate(cs[j][0], v[0], v[1]);
           const f32x2 r1 = rope_rotate(cs[j][1], v[2], v[3]);
@@ -628,21 +654,27 @@ hipError_t launch(const RowGemm& g0, hipStream_t s) {
   return hipGetLastError();
 }
 
+constexpr int kLargeTilings = 3;  // of the six, the first three run the ping-pong loop
+
 // The tiling of least estimated cost; a smaller one must win by 2%. Matrices
 // of 4 GiB or more take one of the large three (the others have no 64-bit
 // loads: such a product has rows or columns for many large tiles).
+int best_tiling(const RowGemm& g) {
+  const double cost[] = {estimate<TBig>(g), estimate<T192>(g),    estimate<TMid>(g),
+                         estimate<T128>(g), estimate<T64x128>(g), estimate<T64>(g)};
+  int best = 0;
+  const int n = buffer_sized(g) ? 6 : kLargeTilings;
+  for (int i = 1; i < n; ++i)
+    if (cost[i] < 0.98 * cost[best]) best = i;
+  return best;
+}
+
 template <int NOUT, int EPI>
 hipError_t launch_best(const RowGemm& g, hipStream_t s) {
   typedef hipError_t (*Launch)(const RowGemm&, hipStream_t);
-  const double cost[] = {estimate<TBig>(g), estimate<T192>(g),    estimate<TMid>(g),
-                         estimate<T128>(g), estimate<T64x128>(g), estimate<T64>(g)};
   static constexpr Launch with[] = {launch<TBig, NOUT, EPI>, launch<T192, NOUT, EPI>,    launch<TMid, NOUT, EPI>,
                                     launch<T128, NOUT, EPI>, launch<T64x128, NOUT, EPI>, launch<T64, NOUT, EPI>};
-  int best = 0;
-  const int n = buffer_sized(g) ? 6 : 3;
-  for (int i = 1; i < n; ++i)
-    if (cost[i] < 0.98 * cost[best]) best = i;
-  return with[best](g, s);
+  return with[best_tiling(g)](g, s);
 }
 
 }  // namespace
@@ -657,6 +689,20 @@ hipError_t launch_row_gemm_bf16(const RowGemm& g, hipStream_t s) {
   if (g.gelu) return launch_best<1, kEpiBf16Gelu>(g, s);
   if (g.residual) return launch_best<1, kEpiBf16Residual>(g, s);
   return launch_best<1, kEpiBf16>(g, s);
+}
+
+hipError_t launch_rms_row_gemm_bf16(const RowGemm& g0, float eps, float* scale, hipStream_t s) {
+  if (g0.M <= 0 || g0.Nc <= 0) return hipSuccess;
+  RowGemm g = g0;
+  if (best_tiling(g) >= kLargeTilings) {
+    g.rms = 1;
+    g.rms_eps = eps;
+  } else {
+    const hipError_t e = launch_row_rms_scale(g.A, true, g.M, g.K, eps, scale, s);
+    if (e != hipSuccess) return e;
+    g.row_scale = scale;
+  }
+  return launch_row_gemm_bf16(g, s);
 }
 
 }  // namespace hsa

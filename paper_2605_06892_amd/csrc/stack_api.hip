@@ -412,7 +412,6 @@ HSA_API int hsa_stack_iteration(const hsa_stack* s, int32_t T, int32_t iter, int
   const bool bf = dt == HSA_STEP_BF16;
   const float scale = 1.0f / sqrtf((float)dh);
   auto ok = [](hipError_t e) { return e == hipSuccess; };
-  auto rms = [&]() { return ok(hsa::launch_row_rms_scale(s->h, bf, n, d, kRmsEps, s->row_scale, stream)); };
   auto attend = [&](const void* q, const void* k, const void* v, int n_kv, const void* k2 = nullptr,
                     const void* v2 = nullptr, int n_split = 0x7fffffff) {
     return ok(bf ? hsa::launch_attention_bf16(q, k, v, s->o, n, n_kv, s->heads, dh, scale, stream,
@@ -422,6 +421,12 @@ HSA_API int hsa_stack_iteration(const hsa_stack* s, int32_t T, int32_t iter, int
                                              v2, n_split));
   };
   auto gemm = [&](const RowGemm& g) { return ok(launch_gemm(dt, g, stream)); };
+  // the product of rms(h)
+  auto rms_gemm = [&](RowGemm g) {
+    if (bf) return ok(hsa::launch_rms_row_gemm_bf16(g, kRmsEps, s->row_scale, stream));
+    g.row_scale = s->row_scale;
+    return ok(hsa::launch_row_rms_scale(s->h, bf, n, d, kRmsEps, s->row_scale, stream)) && gemm(g);
+  };
   if (n > 0) {
     if (!ok(hsa::launch_gather_latent(s->x, s->idx, n, N, C, bf, s->xa, stream)) ||
         !gemm(compact_gemm(s->xa, n, C, s->w_embed, d, nullptr, nullptr, false, s->h)))
@@ -449,7 +454,6 @@ HSA_API int hsa_stack_iteration(const hsa_stack* s, int32_t T, int32_t iter, int
         g.out[2].c_split = (int)n_rows_cache;
       }
       g.n_out = 3;
-      g.row_scale = s->row_scale;
       if (rope) {
         g.rope_cs = reinterpret_cast<const hsa::f32x2*>(s->rope_cs);
         g.rope_tok = s->idx;
@@ -463,29 +467,28 @@ HSA_API int hsa_stack_iteration(const hsa_stack* s, int32_t T, int32_t iter, int
         g.rope_w = s->grid_w;
       }
       const bool split = n_tail > 0;
-      if (!rms() || !gemm(g) ||
+      if (!rms_gemm(g) ||
           !attend(s->q, kc, vc, (int)N, split ? s->k_tail : nullptr, split ? s->v_tail : nullptr,
                   split ? (int)n_rows_cache : 0x7fffffff) ||
           !gemm(compact_gemm(s->o, n, d, w[3], d, nullptr, s->h, false, s->h)))
         return HSA_STEP_ERR_LAUNCH;
       if (Lc > 0) {  // cross-attention of the active rows to the context
         const void* const* wc = s->w_cross + 4 * l;
-        if (!rms() || !gemm(compact_gemm(s->h, n, d, wc[0], d, s->row_scale, nullptr, false, s->q)) ||
+        if (!rms_gemm(compact_gemm(s->h, n, d, wc[0], d, nullptr, nullptr, false, s->q)) ||
             !attend(s->q, wc[2], wc[3], Lc) ||
             !gemm(compact_gemm(s->o, n, d, wc[1], d, nullptr, s->h, false, s->h)))
           return HSA_STEP_ERR_LAUNCH;
       }
       if (F > 0) {  // feed-forward network of the active rows
         const void* const* wf = s->w_ffn + 2 * l;
-        RowGemm up = compact_gemm(s->h, n, d, wf[0], F, s->row_scale, nullptr, false, s->f);
+        RowGemm up = compact_gemm(s->h, n, d, wf[0], F, nullptr, nullptr, false, s->f);
         up.gelu = 1;
-        if (!rms() || !gemm(up) ||
+        if (!rms_gemm(up) ||
             !gemm(compact_gemm(s->f, n, F, wf[1], d, nullptr, s->h, false, s->h)))
           return HSA_STEP_ERR_LAUNCH;
       }
     }
-    if (!rms() ||
-        !gemm(compact_gemm(s->h, n, d, s->w_head, C, s->row_scale, nullptr, bf, s->v_fresh)))
+    if (!rms_gemm(compact_gemm(s->h, n, d, s->w_head, C, nullptr, nullptr, bf, s->v_fresh)))
       return HSA_STEP_ERR_LAUNCH;
   }
 

@@ -242,3 +242,51 @@ def test_attention_bf16_edges(n_q, n_kv, heads, dh, spread):
         H.hsa_attention_core(tq, tk, tv, n_q, heads, dh, dh ** -0.5, out, parts=scratch)
         assert float((out[:n_q].cpu().double() - want).abs().max() / want.abs().max()) < bar
         assert bool((out[n_q] == 7.0).all())
+
+
+@pytest.mark.parametrize("rows,heads,ffn,channels", [(80, 2, 256, 64), (1000, 2, 512, 64), (700, 12, 1536, 64)])
+def test_iteration_small_tilings_form_the_rms_factors(rows, heads, ffn, channels):
+    """One bf16 layer whose products run on the small tilings, which form the rows' RMS factors themselves,
+    against the same calls with hsa_row_rms_scale and its factors."""
+    from paper_2605_06892_amd import stack
+
+    g = torch.Generator(device=DEV).manual_seed(rows)
+    bf, d = torch.bfloat16, heads * 128
+    rn = lambda o, i: (torch.randn(o, i, generator=g, device=DEV) * i ** -0.5).to(bf)  # noqa: E731
+    b = stack.StackBuffers.allocate(rows, channels, 0, heads, 128, bf)
+    b.x = torch.randn(rows, channels, generator=g, device=DEV)
+    b.v_hat = torch.randn(rows, channels, generator=g, device=DEV)
+    b.budget.fill_(4)
+    b.w_embed, b.w_head = rn(d, channels), rn(channels, d)
+    b.layers = [tuple(rn(d, d) for _ in range(4))]
+    b.caches = [(torch.zeros(rows, d, device=DEV, dtype=bf), torch.zeros(rows, d, device=DEV, dtype=bf))]
+    b.ffn = [(rn(ffn, d), rn(d, ffn))]
+    b.f = torch.empty(rows, ffn, device=DEV, dtype=bf)
+    xa = b.x.to(bf)
+    stack.iteration(b, 4, 1, np.array([1, 0.75, 0.5, 0.25, 0], np.float32))
+
+    h = torch.empty(rows, d, device=DEV, dtype=bf)
+    H.hsa_linear(xa, rows, b.w_embed, h)
+    scale = torch.empty(rows, device=DEV)
+    out = lambda n: torch.empty(rows, n, device=DEV, dtype=bf)  # noqa: E731
+
+    def rms_linear(w, y, **kw):
+        H.hsa_row_rms_scale(h, rows, scale)
+        H.hsa_linear(h, rows, w, y, row_scale=scale, **kw)
+        return y
+
+    wq, wk, wv, wo = b.layers[0]
+    q, k, v, o = (rms_linear(w, out(d)) for w in (wq, wk, wv, wv))
+    H.hsa_attention_core(q, k, v, rows, heads, 128, 128 ** -0.5, o, parts=b.attn_parts)
+    H.hsa_linear(o, rows, wo, h, residual=h)
+    f = rms_linear(b.ffn[0][0], out(ffn), gelu=True)
+    H.hsa_linear(f, rows, b.ffn[0][1], h, residual=h)
+    vel = torch.empty(rows, channels, device=DEV)
+    rms_linear(b.w_head, vel)
+    # the factors differ in the last bits of their sums only, so K and V by single bf16 roundings
+    for got, want in zip(b.caches[0], (k, v)):
+        assert bool(((got.float() - want.float()).abs() <= 2.0 ** -7 * want.float().abs() + 1e-6).all())
+        assert float((got != want).float().mean()) < 0.01
+    # each later layer rounds to bf16 what such a difference moved
+    for got, want in ((b.h, h), (b.v_hat, vel)):
+        assert float((got.float() - want.float()).norm() / want.float().norm()) < 2.0 ** -7
