@@ -108,31 +108,33 @@ __device__ __forceinline__ unsigned long long key_bits(unsigned long long k) {
   return ((k & e) == e && (k & 0x000FFFFFFFFFFFFFull)) ? 0x7FF8000000000000ull : k;
 }
 
-// Strategy D accumulation, 16-byte rows. HBM-bound (12 bytes per value): 64
-// tokens per workgroup of two waves, whose rows are read (and v copied to
-// v_prev) with coalesced 16-byte accesses, up to 64 channels at a time, and
-// staged in LDS; then one lane per token adds them in channel order, wave 0 the
-// numerators and wave 1 the denominators. One thread walking each row in
-// global memory took 132 us at 75600 x 64, this takes 24 us (2.4 TB/s).
-constexpr int kL1Tokens = 64, kL1Quads = 16, kL1Threads = 128;
+// Strategy D accumulation, 16-byte rows. HBM-bound (12 bytes per value): one
+// wave takes 32 tokens, whose rows are read (and v copied to v_prev) with
+// coalesced 16-byte accesses, up to 64 channels at a time, and staged in LDS;
+// then one lane per token and sum adds them in channel order, lanes 0-31 the
+// numerators and 32-63 the denominators. At 17 KB of LDS nine such workgroups
+// fit a CU and 75600 tokens are one round, if three waves' registers fit a SIMD:
+// unbounded, the compiler takes 254 (64 tokens on two waves that way: 22.9 us).
+// One thread walking each row in global memory took 132 us at 75600 x 64, this
+// takes 14.5 us (4.0 TB/s).
+constexpr int kL1Tokens = 32, kL1Quads = 16;
 
-__global__ __launch_bounds__(kL1Threads) void l1_rel_accumulate_vec(const f32x4* __restrict__ v,
-                                                                    f32x4* __restrict__ v_prev, long n,
-                                                                    int vpr, double* __restrict__ acc,
-                                                                    int first) {
-  constexpr int LOADS = kL1Tokens * kL1Quads / kL1Threads;
+__global__ __launch_bounds__(kWave, 3) void l1_rel_accumulate_vec(const f32x4* __restrict__ v,
+                                                               f32x4* __restrict__ v_prev, long n,
+                                                               int vpr, double* __restrict__ acc,
+                                                               int first) {
+  constexpr int LOADS = kL1Tokens * kL1Quads / kWave;
   __shared__ f32x4 a[kL1Tokens][kL1Quads + 1], b[kL1Tokens][kL1Quads + 1];
-  __shared__ double den_of[kL1Tokens];
-  const int tid = threadIdx.x, lane = tid & (kWave - 1);
+  const int lane = threadIdx.x, tok = lane % kL1Tokens;
   const long t0 = (long)blockIdx.x * kL1Tokens;
   const int rows = (int)min((long)kL1Tokens, n - t0);
-  double sum = 0.0;  // wave 0: |v - v_prev|_1 of token t0 + lane; wave 1: |v|_1
+  double sum = 0.0;  // lanes 0-31: |v - v_prev|_1 of token t0 + tok; 32-63: |v|_1
   for (int q0 = 0; q0 < vpr; q0 += kL1Quads) {
     const int w = min(kL1Quads, vpr - q0);
     f32x4 va[LOADS], vb[LOADS];
 #pragma unroll
     for (int i = 0; i < LOADS; ++i) {
-      const int f = tid + i * kL1Threads, r = f / w, q = f - r * w;
+      const int f = lane + i * kWave, r = f / w, q = f - r * w;
       if (r < rows) {
         const long e = (t0 + r) * vpr + q0 + q;
         va[i] = v[e];
@@ -142,7 +144,7 @@ __global__ __launch_bounds__(kL1Threads) void l1_rel_accumulate_vec(const f32x4*
     __syncthreads();  // the previous channels are no longer read
 #pragma unroll
     for (int i = 0; i < LOADS; ++i) {
-      const int f = tid + i * kL1Threads, r = f / w, q = f - r * w;
+      const int f = lane + i * kWave, r = f / w, q = f - r * w;
       if (r < rows) {
         v_prev[(t0 + r) * vpr + q0 + q] = va[i];
         if (!first) {
@@ -152,18 +154,17 @@ __global__ __launch_bounds__(kL1Threads) void l1_rel_accumulate_vec(const f32x4*
       }
     }
     __syncthreads();
-    if (!first && lane < rows) {
+    if (!first && tok < rows) {
       for (int q = 0; q < w; ++q) {
-        const f32x4 x = a[lane][q];
-        const f32x4 y = tid < kWave ? b[lane][q] : (f32x4){};
+        const f32x4 x = a[tok][q];
+        const f32x4 y = lane < kL1Tokens ? b[tok][q] : (f32x4){};
 #pragma unroll
         for (int u = 0; u < 4; ++u) sum = sum + fabs((double)x[u] - (double)y[u]);
       }
     }
   }
-  if (tid >= kWave) den_of[lane] = sum;
-  __syncthreads();
-  if (tid < rows) acc[t0 + tid] = first ? 0.0 : acc[t0 + tid] + sum / den_of[tid];
+  const double den = __shfl(sum, kL1Tokens + tok);
+  if (lane < rows) acc[t0 + lane] = first ? 0.0 : acc[t0 + lane] + sum / den;
 }
 
 __global__ __launch_bounds__(kThreads) void l1_rel_accumulate(const float* __restrict__ v,
@@ -269,20 +270,19 @@ __global__ __launch_bounds__(kSelThreads) void select_budgets(const unsigned lon
   // upper half of the key of token t as it is stored, and of its key_bits
   auto load = [&](long t) -> unsigned { return reinterpret_cast<const unsigned*>(keys)[2 * min(t, (long)n - 1) + 1]; };
   auto top_bits = [&](unsigned hi, long t) -> unsigned {
-    if (t >= n) return kNone;
-    if ((hi & 0x7FF00000u) == 0x7FF00000u) return (unsigned)(key_bits(keys[t]) >> 32);  // infinite or NaN
+    hi = t < n ? hi : kNone;
+    if ((hi & 0x7FF00000u) == 0x7FF00000u && t < n)  // infinite or NaN
+      return (unsigned)(key_bits(keys[t]) >> 32);
     return hi;
   };
   unsigned top[KEYS > 0 ? KEYS : 1];
   if constexpr (KEYS > 0) {
-    // buffer loads: one lane offset and a scalar step, no address per load
+    // buffer loads: one lane offset and a scalar step, no address per load;
+    // past the last token they return 0, which top_bits replaces
     const auto rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<u64*>(keys), 0, n * 8, 0x00020000);
 #pragma unroll
-    for (int i = 0; i < KEYS; ++i) {
-      top[i] = kNone;
-      if (i * kSelThreads + tid < n)
-        top[i] = __builtin_amdgcn_raw_buffer_load_b32(rs, tid * 8 + 4, i * kSelThreads * 8, 0);
-    }
+    for (int i = 0; i < KEYS; ++i)
+      top[i] = __builtin_amdgcn_raw_buffer_load_b32(rs, tid * 8 + 4, i * kSelThreads * 8, 0);
 #pragma unroll
     for (int i = 0; i < KEYS; ++i) top[i] = top_bits(top[i], i * kSelThreads + tid);
   }
@@ -373,8 +373,14 @@ __global__ __launch_bounds__(kSelThreads) void select_budgets(const unsigned lon
   const int shift32 = bits > kSelBinBits ? bits - kSelBinBits : 0;
   const u64 lo = (u64)lo32 << 32;  // the bins in whole keys
   const int shift = shift32 + 32;
-  auto bin32 = [&](unsigned k) { return k == kNone ? kSelBins : (int)((k - lo32) >> shift32); };
-  each([&](unsigned k, long) { atomicAdd(&hist[bin32(k)], 1); });
+  auto bin32 = [&](unsigned k) { return k == kNone ? (unsigned)kSelBins : (k - lo32) >> shift32; };
+  // the held keys become their bins: found once, and no lane mask of k == kNone per key stays live
+  if constexpr (KEYS > 0) {
+#pragma unroll
+    for (int i = 0; i < KEYS; ++i) top[i] = bin32(top[i]);
+  }
+  auto bin_at = [&](unsigned k) { return KEYS > 0 ? k : bin32(k); };
+  each([&](unsigned k, long) { atomicAdd(&hist[bin_at(k)], 1); });
 
   {
     int c[kPer];
@@ -422,14 +428,14 @@ __global__ __launch_bounds__(kSelThreads) void select_budgets(const unsigned lon
       }
       last = g;
     }
+    hist[kSelBins] = kSelBig;  // no token: nothing to write
     slot_off[slots] = fill;
     n_slots = slots;
     n_big = big;
   }
   __syncthreads();
   each([&](unsigned k, long t) {
-    const int code = hist[bin32(k)];
-    if (t >= n) return;
+    const int code = hist[bin_at(k)];
     if (code >= 0) {
       budget[t] = code;
     } else if (code != kSelBig) {
@@ -733,7 +739,7 @@ hipError_t launch_l1_rel(const float* v, float* v_prev, long n_tokens, int chann
   const uintptr_t align = reinterpret_cast<uintptr_t>(v) | reinterpret_cast<uintptr_t>(v_prev);
   if (channels % 4 == 0 && channels > 0 && align % 16 == 0)
     hipLaunchKernelGGL(l1_rel_accumulate_vec, dim3((unsigned)((n_tokens + kL1Tokens - 1) / kL1Tokens)),
-                       dim3(kL1Threads), 0, s, reinterpret_cast<const f32x4*>(v),
+                       dim3(kWave), 0, s, reinterpret_cast<const f32x4*>(v),
                        reinterpret_cast<f32x4*>(v_prev), n_tokens, channels / 4, acc, first ? 1 : 0);
   else
     hipLaunchKernelGGL(l1_rel_accumulate, dim3(grid_for(n_tokens)), dim3(kThreads), 0, s, v, v_prev,

@@ -290,3 +290,18 @@ def test_iteration_small_tilings_form_the_rms_factors(rows, heads, ffn, channels
     # each later layer rounds to bf16 what such a difference moved
     for got, want in ((b.h, h), (b.v_hat, vel)):
         assert float((got.float() - want.float()).norm() / want.float().norm()) < 2.0 ** -7
+
+
+@pytest.mark.parametrize("pinned", [True, False])
+@pytest.mark.parametrize("slot", [0, 3, 7])
+@pytest.mark.parametrize("n", [1, 5000, 32760])
+def test_active_set_count_into_host_memory(pinned, slot, n):
+    """The count lands in its own element of a host buffer, inside pinned memory (written by the
+    kernel) as in pageable memory (copied), and nowhere else."""
+    budget = torch.tensor([8, 4], dtype=torch.int32)[torch.arange(n) % 2].to(DEV)  # iteration 1: the 8s
+    idx, count = torch.empty(n, dtype=torch.int32, device=DEV), torch.empty(1, dtype=torch.int32, device=DEV)
+    host = torch.full((8,), -77, dtype=torch.int32, pin_memory=pinned)
+    want = (n + 1) // 2
+    assert H.hsa_build_active_set(budget, 8, 1, 0, idx, count, host_buf=host[slot:]) == want
+    assert host.tolist() == [want if i == slot else -77 for i in range(8)]
+    assert int(count) == want and torch.equal(idx[:want].cpu(), torch.arange(0, n, 2, dtype=torch.int32))
