@@ -3,7 +3,7 @@
 //   * gather_latent: the fp32 latent rows of the active tokens, converted to
 //     the model dtype, as the compact input of the patch embedding (Section
 //     2.3: only the active rows flow through the model).
-//   * velocity_keys + select_budgets: the group refresh. Group sizes are fixed
+//   * velocity_keys + rank_budgets / select_budgets: the group refresh. Group sizes are fixed
 //     and membership follows a per-token velocity ranking (Section 2.2,
 //     Appendix B): the key of a token is the squared L2 norm of its velocity,
 //     a float64 sum of the exact squares in channel order, and its rank is
@@ -231,20 +231,63 @@ __global__ __launch_bounds__(kThreads) void velocity_keys_scalar(const float* __
 //   3. every token reads its bin's budget; the keys of the bins with a boundary
 //      inside, a few dozen, are collected and ranked by comparing all pairs.
 // A bin too full for that (an outlier that widens the range, or many equal
-// keys) is divided again around each of its boundaries, first by key, then,
-// among equal keys, by token index, until the boundary's element (key, token)
-// is found; its keys are then compared with those elements.
+// keys) is divided again, first by key, from the least to the greatest it
+// holds, then, among equal keys, by token index, around each of its boundaries
+// until the boundary's element (key, token) is found; its keys are then compared
+// with those elements.
 // Steps 1 and 2 and the lookup of 3 use the upper halves of the keys (sign,
 // exponent and 20 mantissa bits), which stay in registers for up to 81920
 // tokens; whole keys are read again for the collected ones only. The bound is
 // one CU's loads, LDS atomics and instruction fetches; spreading the steps over
 // CUs needs scratch memory and more launches, at 3 us each, than it saves.
 // Comparing all pairs of keys on the whole chip took 303 us at 32760 tokens and
-// 1125 us at 75600, this takes 17 and 42 us (26 and 59 with whole keys in
-// registers, or read from L2 by every step).
+// 1125 us at 75600, this takes 17 and 39 us (26 and 59 with whole keys in
+// registers, or read from L2 by every step), and with all keys equal 94 and 217.
 constexpr int kSelThreads = 1024, kSelBinBits = 13, kSelBins = 1 << kSelBinBits;
 constexpr int kSelList = 1024;     // collected keys
 constexpr int kSelBig = -64;       // histogram code of a bin too full for the list
+
+// Few keys: all pairs, 16 tokens a workgroup, so 4096 keys give every CU one.
+// All keys are in LDS and 64 slices of them count for each token, which takes
+// 5.6 us a call at 1000 keys, 6.3 at 4096 and 10.2 at 5000 whatever the keys are
+// (10.6, 35.5 and 43.8 with 64 tokens on four waves). select_budgets takes 12,
+// 11 and 10.7 us, 23 to 43 if many keys are equal; at 5500 keys the ordinary
+// case is level (11.0 and 10.2) and at 6144 it is the faster one (10.5 to 11.7).
+constexpr int kRankTokens = 16, kRankMax = 5120;
+__global__ __launch_bounds__(kSelThreads) void rank_budgets(const unsigned long long* __restrict__ keys, int n,
+                                                            GroupTable tab, int32_t* __restrict__ budget) {
+  constexpr int kSlices = kSelThreads / kRankTokens;
+  __shared__ unsigned long long key[kRankMax];
+  __shared__ int partial[kSlices][kRankTokens];
+  const int tid = threadIdx.x, tok = tid % kRankTokens, slice = tid / kRankTokens;
+  const int t = blockIdx.x * kRankTokens + tok;
+#pragma unroll
+  for (int i = 0; i < kRankMax / kSelThreads; ++i) {
+    const int e = tid + i * kSelThreads;
+    if (e < n) key[e] = key_bits(keys[e]);
+  }
+  __syncthreads();
+  const unsigned long long kt = key[min(t, n - 1)];
+  int count = 0;
+#pragma unroll 8
+  for (int e = slice; e < n; e += kSlices) {
+    const unsigned long long km = key[e];
+    count += (km < kt) | ((km == kt) & (e < t));
+  }
+  partial[slice][tok] = count;
+  __syncthreads();
+  if (tid >= kWave) return;
+  int r = 0;  // of the lanes' 16 slices, then of all four lanes of a token
+#pragma unroll
+  for (int w = 0; w < kSlices; w += kWave / kRankTokens) r += partial[w + slice][tok];
+  r += __shfl_xor(r, 16);
+  r += __shfl_xor(r, 32);
+  if (slice > 0 || t >= n) return;
+  int g = 0;
+  while (g + 1 < tab.n && r >= tab.end[g]) ++g;
+  budget[t] = tab.budget[g];
+}
+
 // KEYS: upper halves per thread in registers (0: read by each step)
 template <int KEYS>
 __global__ __launch_bounds__(kSelThreads) void select_budgets(const unsigned long long* __restrict__ keys,
@@ -262,10 +305,14 @@ __global__ __launch_bounds__(kSelThreads) void select_budgets(const unsigned lon
   __shared__ int bin_of[kMaxGroups], before_of[kMaxGroups], count_of[kMaxGroups], slot_of[kMaxGroups];
   __shared__ int slot_off[kMaxGroups + 1], slot_fill[kMaxGroups], slot_before[kMaxGroups], n_slots, n_big;
   __shared__ int sub_bin, sub_before, sub_count;
+  __shared__ u64 min_of[kWaves], max_of[kWaves];
   __shared__ u64 thr_key[kMaxGroups];
   __shared__ int thr_tok[kMaxGroups];
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
   const int nb = tab.n - 1;  // boundaries
+  // The most keys of one bin that are ranked, at 80 ns each; dividing a bin
+  // takes a few more reads of all keys, 0.2 ns a key and 2 us each.
+  const int cap = min(kSelList, max(256, n / 100));
 
   // upper half of the key of token t as it is stored, and of its key_bits
   auto load = [&](long t) -> unsigned { return reinterpret_cast<const unsigned*>(keys)[2 * min(t, (long)n - 1) + 1]; };
@@ -305,8 +352,16 @@ __global__ __launch_bounds__(kSelThreads) void select_budgets(const unsigned lon
   };
   // f(key bits, token), for the steps that only the division of full bins takes
   auto each_again = [&](auto&& f) __attribute__((always_inline)) {
+    constexpr int V = 8;
 #pragma unroll 1
-    for (long t = tid; t < n; t += kSelThreads) f(key_bits(keys[t]), (int)t);
+    for (long t0 = tid; t0 < n; t0 += (long)V * kSelThreads) {
+      u64 k[V];
+#pragma unroll
+      for (int i = 0; i < V; ++i) k[i] = keys[min(t0 + (long)i * kSelThreads, (long)n - 1)];
+#pragma unroll
+      for (int i = 0; i < V; ++i)
+        if (t0 + (long)i * kSelThreads < n) f(key_bits(k[i]), (int)(t0 + (long)i * kSelThreads));
+    }
   };
   auto clear_hist = [&]() {
 #pragma unroll
@@ -380,7 +435,11 @@ __global__ __launch_bounds__(kSelThreads) void select_budgets(const unsigned lon
     for (int i = 0; i < KEYS; ++i) top[i] = bin32(top[i]);
   }
   auto bin_at = [&](unsigned k) { return KEYS > 0 ? k : bin32(k); };
-  each([&](unsigned k, long) { atomicAdd(&hist[bin_at(k)], 1); });
+  if (bits > 0) {
+    each([&](unsigned k, long) { atomicAdd(&hist[bin_at(k)], 1); });
+  } else if (tid == 0) {
+    hist[0] = n;  // one bin, without an atomic per key on one address
+  }
 
   {
     int c[kPer];
@@ -416,7 +475,7 @@ __global__ __launch_bounds__(kSelThreads) void select_budgets(const unsigned lon
       if (bin_of[g] < 0) continue;
       if (last >= 0 && bin_of[last] == bin_of[g]) {
         slot_of[g] = slot_of[last];
-      } else if (count_of[g] <= kSelList - fill) {
+      } else if (count_of[g] <= min(cap, kSelList - fill)) {
         slot_off[slots] = fill;
         slot_before[slots] = before_of[g];
         fill += count_of[g];
@@ -457,22 +516,73 @@ __global__ __launch_bounds__(kSelThreads) void select_budgets(const unsigned lon
   }
   if (!n_big) return;
 
+  struct Range {  // keys k0 .. k0 + 2^ks - 1 of tokens t0 .. t0 + 2^ts - 1
+    u64 k0;
+    int ks, t0, ts;
+  };
+  auto inside = [](const Range& r, u64 k, int t) {
+    return k >= r.k0 && (k - r.k0) >> r.ks == 0 && t >= r.t0 && (t - r.t0) >> r.ts == 0;
+  };
+  auto step_of = [](const Range& r) { return max((r.ks > 0 ? r.ks : r.ts) - kSelBinBits, 0); };
+  // Histogram of a range by key, drawn in to its keys first, or by token if they
+  // are equal: counts of this thread's bins, and the keys before the first of them.
+  auto divide = [&](Range& r, int (&c)[kPer]) __attribute__((always_inline)) -> int {
+    if (r.ks > 0) {
+      u64 a = ~0ull, b = 0;
+      each_again([&](u64 k, int t) {
+        if (!inside(r, k, t)) return;
+        a = min(a, k);
+        b = max(b, k);
+      });
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) {
+        a = min(a, (u64)__shfl_xor(a, o));
+        b = max(b, (u64)__shfl_xor(b, o));
+      }
+      if (lane == 0) {
+        min_of[wave] = a;
+        max_of[wave] = b;
+      }
+      __syncthreads();
+      for (int w = 0; w < kWaves; ++w) {
+        a = min(a, min_of[w]);
+        b = max(b, max_of[w]);
+      }
+      r.k0 = a;
+      r.ks = b > a ? 64 - __clzll(b - a) : 0;
+    }
+    clear_hist();
+    const int sh = step_of(r);
+    each_again([&](u64 k, int t) {
+      if (inside(r, k, t)) atomicAdd(&hist[r.ks > 0 ? (int)((k - r.k0) >> sh) : (t - r.t0) >> sh], 1);
+    });
+    return scan_bins(c);
+  };
+  Range bin = {};
+  int bin_c[kPer] = {}, bin_p = 0;
   for (int g = 0; g < nb; ++g) {  // the element of each boundary inside a bin that did not fit
     if (bin_of[g] < 0 || slot_of[g] >= 0) continue;
     const int e = end_at[g];
-    u64 k0 = lo + ((u64)bin_of[g] << shift);
-    int ks = shift, t0 = 0, ts = 32 - __clz(n);  // keys k0 .. k0 + 2^ks - 1, tokens t0 .. t0 + 2^ts - 1
-    int before = before_of[g], count = count_of[g];
-    while (count > kSelList) {
-      const bool by_key = ks > 0;
-      const int bits_left = by_key ? ks : ts, sh = bits_left > kSelBinBits ? bits_left - kSelBinBits : 0;
-      clear_hist();
-      each_again([&](u64 k, int t) {
-        if (k >= k0 && (k - k0) >> ks == 0 && t >= t0 && (t - t0) >> ts == 0)
-          atomicAdd(&hist[by_key ? (int)((k - k0) >> sh) : (t - t0) >> sh], 1);
-      });
-      int c[kPer];
-      int p = before + scan_bins(c);
+    const bool known = g > 0 && bin_of[g - 1] == bin_of[g];  // divided for the boundary before
+    Range r = known ? bin : Range{lo + ((u64)bin_of[g] << shift), shift, 0, 32 - __clz(n)};
+    int before = before_of[g], count;
+    bool whole = true;  // r is still the whole bin
+    do {
+      int c[kPer], p;
+      if (whole && known) {
+        p = bin_p;
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) c[i] = bin_c[i];
+      } else {
+        p = divide(r, c);
+        if (whole) {
+          bin = r;
+          bin_p = p;
+#pragma unroll
+          for (int i = 0; i < kPer; ++i) bin_c[i] = c[i];
+        }
+      }
+      p += before;
 #pragma unroll
       for (int i = 0; i < kPer; ++i) {
         if (e >= p && e - p < c[i]) {
@@ -483,21 +593,24 @@ __global__ __launch_bounds__(kSelThreads) void select_budgets(const unsigned lon
         p += c[i];
       }
       __syncthreads();
-      if (by_key) {
-        k0 += (u64)sub_bin << sh;
-        ks = sh;
+      const int sh = step_of(r);
+      if (r.ks > 0) {
+        r.k0 += (u64)sub_bin << sh;
+        r.ks = sh;
       } else {
-        t0 += sub_bin << sh;
-        ts = sh;
+        r.t0 += sub_bin << sh;
+        r.ts = sh;
       }
       before = sub_before;
       count = sub_count;
-    }
+      whole = false;
+      __syncthreads();  // sub_* are read
+    } while (count > cap);
     __syncthreads();  // the list is no longer read
     if (tid == 0) slot_fill[0] = 0;
     __syncthreads();
     each_again([&](u64 k, int t) {
-      if (k >= k0 && (k - k0) >> ks == 0 && t >= t0 && (t - t0) >> ts == 0) {
+      if (inside(r, k, t)) {
         const int at = atomicAdd(&slot_fill[0], 1);
         list_key[at] = k;
         list_tok[at] = t;
@@ -722,6 +835,11 @@ hipError_t launch_rank_budgets(const double* keys, long n_tokens, const GroupTab
                                int32_t* budget, hipStream_t s) {
   if (n_tokens <= 0) return hipSuccess;
   const auto* k = reinterpret_cast<const unsigned long long*>(keys);
+  if (n_tokens <= kRankMax) {
+    hipLaunchKernelGGL(rank_budgets, dim3((unsigned)((n_tokens + kRankTokens - 1) / kRankTokens)),
+                       dim3(kSelThreads), 0, s, k, (int)n_tokens, tab, budget);
+    return hipGetLastError();
+  }
   auto launch = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, dim3(1), dim3(kSelThreads), 0, s, k, (int)n_tokens, tab, budget);
   };

@@ -124,7 +124,7 @@ def _keys(pattern, n, rng):
 
 
 # tokens around a wave, the workgroup, the list, the register-resident limit (32768)
-@pytest.mark.parametrize("n", [1, 2, 63, 1025, 4097, 32768, 32769, 75601])
+@pytest.mark.parametrize("n", [1, 2, 17, 63, 1025, 4097, 5120, 5121, 8193, 32768, 32769, 75601])
 @pytest.mark.parametrize("pattern", ["chi2", "equal", "two_values", "outliers", "many_nan", "negative", "lognormal"])
 @pytest.mark.parametrize("n_groups", [1, 3, 16])
 def test_assign_budgets_by_key_edges(n, pattern, n_groups):
