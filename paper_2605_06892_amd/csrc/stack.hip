@@ -324,12 +324,16 @@ __global__ __launch_bounds__(kSelThreads) void select_budgets(const unsigned lon
   };
   unsigned top[KEYS > 0 ? KEYS : 1];
   if constexpr (KEYS > 0) {
-    // buffer loads: one lane offset and a scalar step, no address per load;
-    // past the last token they return 0, which top_bits replaces
-    const auto rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<u64*>(keys), 0, n * 8, 0x00020000);
+    // buffer loads, each through a resource over the keys from its row of
+    // kSelThreads on: the address steps are scalar, and past the last token a load
+    // returns 0, which top_bits replaces. (The range check covers the lane's offset
+    // alone; a step in the scalar offset would pass it.)
 #pragma unroll
-    for (int i = 0; i < KEYS; ++i)
-      top[i] = __builtin_amdgcn_raw_buffer_load_b32(rs, tid * 8 + 4, i * kSelThreads * 8, 0);
+    for (int i = 0; i < KEYS; ++i) {
+      const auto rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<u64*>(keys + i * kSelThreads), 0,
+                                                        max(n - i * kSelThreads, 0) * 8, 0x00020000);
+      top[i] = __builtin_amdgcn_raw_buffer_load_b32(rs, tid * 8 + 4, 0, 0);
+    }
 #pragma unroll
     for (int i = 0; i < KEYS; ++i) top[i] = top_bits(top[i], i * kSelThreads + tid);
   }

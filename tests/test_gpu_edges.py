@@ -144,6 +144,19 @@ def test_assign_budgets_by_key_edges(n, pattern, n_groups):
     assert int(out[n]) == -5
 
 
+@pytest.mark.parametrize("n", [5121, 8193, 32769, 81919])
+def test_assign_budgets_by_key_at_the_end_of_an_allocation(n):
+    """The keys are the last bytes of a 32 MiB device allocation, a segment of its own: a read past them leaves it."""
+    rng = np.random.default_rng(n)
+    keys = rng.chisquare(64, n)
+    whole = torch.empty((32 << 20) // 8, dtype=torch.float64, device=DEV)
+    whole[-n:] = torch.from_numpy(keys)
+    groups = [(1, n // 3), (2, n // 3), (4, n - 2 * (n // 3))]
+    out = torch.empty(n, dtype=torch.int32, device=DEV)
+    H.hsa_assign_budgets_by_key(whole[-n:], 4, groups, out)
+    assert np.array_equal(out.cpu().numpy(), _ranked_budgets(keys, groups))
+
+
 # tokens around the 64 of a workgroup, channels around the 64 of a chunk and off the 16-byte path
 @pytest.mark.parametrize("n", [1, 63, 64, 65, 1000])
 @pytest.mark.parametrize("channels", [4, 16, 62, 64, 68, 200])
