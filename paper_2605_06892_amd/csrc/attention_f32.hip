@@ -138,11 +138,14 @@ __global__ __launch_bounds__(kThreads) void attention_f32_kernel(
 
   // Rows n0 .. n0+31 of the keys or values are read through a buffer resource
   // at row n0 (uniform, so scalar), with the lane's byte offset and the row
-  // step in the two offsets of the load: no address arithmetic per load. Rows
-  // past n_kv repeat the last one and are masked out of the softmax.
+  // step in the two offsets of the load: no address arithmetic per load. The
+  // resource ends at row n_kv, and in the last block, where the step is part of the
+  // lane's offset, the one that is range-checked, rows past it read as zeros: their
+  // scores are masked, and 0 times a zero adds nothing to an output.
   auto first = [&](const float* a, const float* a2, int n0) {
     const float* b = (SPLIT && n0 >= n_split) ? a2 + (long)(n0 - n_split) * d + col0 : a + (long)n0 * d;
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(b), 0, -1, 0x00020000);
+    const unsigned bytes = (unsigned)min(kKeys, n_kv - n0) * (unsigned)(d * 4) - (unsigned)(col0 * 4);
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(b), 0, (int)bytes, 0x00020000);
   };
   auto by_row = [&](int n0) {
     return SPLIT && (d > kMaxOffsetRow || (n0 < n_split && n0 + kKeys > n_split));
@@ -155,12 +158,13 @@ __global__ __launch_bounds__(kThreads) void attention_f32_kernel(
       const int n = min(n0 + r + step, n_kv - 1);
       const float* src = n >= n_split ? a2 + (long)(n - n_split) * d + col0 : a + (long)n * d;
       __builtin_memcpy(dst, src + c, sizeof(*dst));
+      if (n0 + r + step >= n_kv) __builtin_memset(dst, 0, sizeof(*dst));
       return;
     }
     const auto rs = first(a, a2, n0);
     int vo = r * row_bytes + c * 4, so = step * row_bytes;
     if (n0 + kKeys > n_kv) {
-      vo = min(r + step, n_kv - 1 - n0) * row_bytes + c * 4;
+      vo += so;
       so = 0;
     }
     if constexpr (C == 2) {

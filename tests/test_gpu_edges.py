@@ -65,6 +65,24 @@ def test_attention_f32_infinite_and_nan_scores():
     assert torch.isnan(got[1]).all()
 
 
+@pytest.mark.parametrize("dh", [64, 128])
+@pytest.mark.parametrize("n_kv", [1, 33, 256, 300])
+def test_attention_f32_infinite_value_in_the_last_row(n_kv, dh):
+    """Rows past n_kv take no part, so an infinite value of the last row stays itself. The scores are equal: every
+    row has weight."""
+    g = _gen(n_kv)
+    q, k, v = torch.randn(20, dh, generator=g), torch.ones(n_kv, dh), torch.randn(n_kv, dh, generator=g)
+    v[-1, 3], v[-1, 5] = float("inf"), -float("inf")
+    out = torch.empty(20, dh, device=DEV)
+    H.hsa_attention_core(q.to(DEV), k.to(DEV), v.to(DEV), 20, 1, dh, dh ** -0.5, out)
+    want = v.double().mean(0)
+    got = out.cpu().double()
+    assert bool((got[:, 3] == float("inf")).all()) and bool((got[:, 5] == -float("inf")).all())
+    finite = want.isfinite()
+    # equal weights: n_kv additions of values of size 1, each a few ulps off at most
+    assert float((got[:, finite] - want[finite]).abs().max()) < 2.0 ** -24 * (16 + n_kv)
+
+
 # rows and columns around the 32 and 64 tiles, k around the 4-float loads and the slabs; 300 x 96 x 3
 # outputs take the split-k tiles, 1500 x 1100 the 64 x 64 tiles on 256 compute units
 @pytest.mark.parametrize("m,n,k", [(1, 1, 1), (31, 33, 3), (33, 31, 63), (65, 64, 64), (300, 96, 65), (1500, 1100, 37),
