@@ -131,6 +131,10 @@ __global__ __launch_bounds__(kThreads) void attention_f32_kernel(
     else return qf[j];
   };
 
+  // Maxima are of the products q.k and the scale follows the subtraction: the
+  // exponents (q.k - m) scale are then at most 0 however large the products are. (With
+  // q.k scale - fl(m scale) in one FMA they carry what rounding m scale lost, which is
+  // over 88 and overflows the exponential from scores of about 1e9 on.)
   Acc acc[DT];
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt) acc[dt] = (Acc){};
@@ -237,11 +241,10 @@ __global__ __launch_bounds__(kThreads) void attention_f32_kernel(
       for (int e = 0; e < NE; ++e) mx = fmaxf(mx, s[kt][e]);
 #pragma unroll
     for (int x = W; x < kWave; x <<= 1) mx = fmaxf(mx, __shfl_xor(mx, x));
-    mx *= scale;  // scale > 0
     if (__any(mx > m_run)) {
       // raise the running maximum (wave-uniform branch, rare after the first blocks)
       const float m_new = fmaxf(m_run, mx);
-      const float alpha = m_run == -INFINITY ? 0.f : expf(m_run - m_new);
+      const float alpha = m_run == -INFINITY ? 0.f : expf((m_run - m_new) * scale);
       l_run *= alpha;
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt) acc[dt] *= alpha;
@@ -253,7 +256,7 @@ __global__ __launch_bounds__(kThreads) void attention_f32_kernel(
     for (int kt = 0; kt < KT; ++kt)
 #pragma unroll
       for (int e = 0; e < NE; ++e) {
-        s[kt][e] = exp_neg(fmaf(s[kt][e], scale, -m_use));
+        s[kt][e] = exp_neg((s[kt][e] - m_use) * scale);
         ls += s[kt][e];
       }
     l_run += ls;
@@ -293,7 +296,7 @@ __global__ __launch_bounds__(kThreads) void attention_f32_kernel(
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) {
       const float mw = m_part[w][r];
-      const float wt = mw == -INFINITY ? 0.f : expf(mw - m);  // 0: no finite score (or no key) in this wave
+      const float wt = mw == -INFINITY ? 0.f : expf((mw - m) * scale);  // 0: no finite score (or no key) in this wave
       l = fmaf(wt, l_part[w][r], l);
       const f32x4 a = *reinterpret_cast<const f32x4*>(&buf[w][r * P + c]);
 #pragma unroll

@@ -83,6 +83,20 @@ def test_attention_f32_infinite_value_in_the_last_row(n_kv, dh):
     assert float((got[:, finite] - want[finite]).abs().max()) < 2.0 ** -24 * (16 + n_kv)
 
 
+@pytest.mark.parametrize("dh", [64, 128])
+@pytest.mark.parametrize("size", [1e2, 1e4, 3e4, 1e6])
+def test_attention_f32_large_scores(size, dh):
+    """Scores up to 1e13: every row's softmax is its largest score alone, as the gaps between them are."""
+    g = _gen(int(size))
+    q, k, v = (torch.randn(n, dh, generator=g) for n in (20, 300, 300))
+    q, k = q * size, k * size
+    want = _attend64(q, k, v, 1)
+    out = torch.empty(20, dh, device=DEV)
+    H.hsa_attention_core(q.to(DEV), k.to(DEV), v.to(DEV), 20, 1, dh, dh ** -0.5, out)
+    # weights 1 and 0: a sum, a merge and a division of one value
+    assert float((out.cpu().double() - want).abs().max()) < 2.0 ** -22 * float(v.abs().max())
+
+
 # rows and columns around the 32 and 64 tiles, k around the 4-float loads and the slabs; 300 x 96 x 3
 # outputs take the split-k tiles, 1500 x 1100 the 64 x 64 tiles on 256 compute units
 @pytest.mark.parametrize("m,n,k", [(1, 1, 1), (31, 33, 3), (33, 31, 63), (65, 64, 64), (300, 96, 65), (1500, 1100, 37),
