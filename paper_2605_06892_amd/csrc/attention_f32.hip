@@ -93,6 +93,9 @@ __global__ __launch_bounds__(kThreads) void attention_f32_kernel(
   constexpr int P = DH + 4;            // padded LDS row, floats
   constexpr bool kQLds = DH > 64 && W > 16;
   typedef float vrow __attribute__((ext_vector_type(DT)));
+  // the same in a row of the merge buffer, whose stride of P floats is a multiple of 16 bytes and no more
+  typedef vrow vrow_lds __attribute__((aligned(DT < 4 ? 4 * DT : 16)));
+  static_assert(P * 4 % alignof(vrow_lds) == 0, "rows of the merge buffer are aligned for its stores");
   // per wave: its block's K rows, at the end its share of the output
   __shared__ __attribute__((aligned(16))) float buf[kWaves][kKeys * P];
   __shared__ float m_part[kWaves][W], l_part[kWaves][W];
@@ -281,7 +284,7 @@ __global__ __launch_bounds__(kThreads) void attention_f32_kernel(
     vrow r;
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt) r[dt] = acc[dt][e];
-    *reinterpret_cast<vrow*>(&kl[lw * P + Mfma<W>::row(e, slot) * DT]) = r;
+    *reinterpret_cast<vrow_lds*>(&kl[lw * P + Mfma<W>::row(e, slot) * DT]) = r;
   }
   __syncthreads();
   for (int f = threadIdx.x; f < W * CPR; f += kThreads) {
