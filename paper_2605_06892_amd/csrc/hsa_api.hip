@@ -55,7 +55,10 @@ HSA_API int hsa_build_active_set_window(const int32_t* budget, int64_t n_tokens,
     return HSA_STEP_ERR_ALIAS;
   // Into pinned host memory the kernel writes the count itself; a copy behind it
   // is a launch of its own (27.4 against 25.9 us for the whole call at 32760 tokens).
+  // An element of the call's own arrays, pinned memory too, waits for the copy: other
+  // workgroups may still read or write it when the last one has the count.
   int32_t* host_dev = n_active_host ? device_view(n_active_host) : nullptr;
+  if (overlaps(host_dev, 4, budget, nb) || overlaps(host_dev, 4, idx, nb)) host_dev = nullptr;
   hipError_t e = hsa::launch_active_set(budget, (int)n_tokens, T, iter, margin, outside_period, idx,
                                         n_active_dev, stream, host_dev);
   if (e != hipSuccess) return HSA_STEP_ERR_LAUNCH;

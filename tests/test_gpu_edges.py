@@ -350,3 +350,22 @@ def test_active_set_count_into_host_memory(pinned, slot, n):
     assert H.hsa_build_active_set(budget, 8, 1, 0, idx, count, host_buf=host[slot:]) == want
     assert host.tolist() == [want if i == slot else -77 for i in range(8)]
     assert int(count) == want and torch.equal(idx[:want].cpu(), torch.arange(0, n, 2, dtype=torch.int32))
+
+
+@pytest.mark.parametrize("inside", ["budget", "idx"])
+def test_active_set_count_inside_the_calls_own_arrays(inside):
+    """Budgets and indices in pinned memory with the host's count one of their elements: all of them are read and
+    written before the count lands."""
+    n = 32760
+    budget = torch.tensor([8, 4], dtype=torch.int32)[torch.arange(n) % 2].pin_memory()
+    idx = torch.full((n,), -7, dtype=torch.int32, pin_memory=True)
+    count = torch.empty(1, dtype=torch.int32, device=DEV)
+    array, slot = {"budget": (budget, 3), "idx": (idx, 5)}[inside]
+    st = H.lib().hsa_build_active_set(budget.data_ptr(), n, 8, 1, 0, idx.data_ptr(), count.data_ptr(),
+                                      array[slot:].data_ptr(), torch.cuda.current_stream().cuda_stream)
+    assert st == 0
+    want = torch.arange(0, n, 2, dtype=torch.int32)
+    if inside == "idx":
+        want[slot] = n // 2
+    assert torch.equal(idx[:n // 2], want) and bool((idx[n // 2:] == -7).all())
+    assert int(count) == n // 2 and int(array[slot]) == n // 2
