@@ -230,19 +230,23 @@ __global__ __launch_bounds__(kThreads) void velocity_keys_scalar(const float* __
 //      has one group, whose budget replaces its count;
 //   3. every token reads its bin's budget; the keys of the bins with a boundary
 //      inside, a few dozen, are collected and ranked by comparing all pairs.
-// A bin too full for that (an outlier that widens the range, or many equal
-// keys) is divided again, first by key, from the least to the greatest it
-// holds, then, among equal keys, by token index, around each of its boundaries
-// until the boundary's element (key, token) is found; its keys are then compared
-// with those elements.
+// Bins too full for that (an outlier that widens the range, or many equal
+// keys) are divided again, all at once, first by key, from the least to the greatest
+// one holds, then, among equal keys, by token index, around their boundaries
+// until every boundary's element (key, token) is found; their keys are then compared
+// with those elements. (One boundary after the other, 16 groups of keys of 16 values
+// took 168 us at 5121 keys and 503 at 32760, where all pairs take 45 and 295; at once
+// 38 and 171.)
 // Steps 1 and 2 and the lookup of 3 use the upper halves of the keys (sign,
 // exponent and 20 mantissa bits), which stay in registers for up to 81920
 // tokens; whole keys are read again for the collected ones only. The bound is
-// one CU's loads, LDS atomics and instruction fetches; spreading the steps over
-// CUs needs scratch memory and more launches, at 3 us each, than it saves.
-// Comparing all pairs of keys on the whole chip took 303 us at 32760 tokens and
-// 1125 us at 75600, this takes 17 and 39 us (26 and 59 with whole keys in
-// registers, or read from L2 by every step), and with all keys equal 94 and 217.
+// one CU's loads, LDS atomics and instruction fetches. Spreading the steps over
+// CUs would take two or more further launches, at 3 us each.
+// Comparing all pairs of keys on the whole chip took 297 us at 32760 tokens and
+// 1110 us at 75600, this takes 16 and 31 us (keys without structure, 4 groups), 88 and
+// 207 with all keys equal. It is slower than all pairs in one corner: 16 groups, and an
+// outlier that puts all other keys, of a few values, into one bin (50 against 45 us at
+// 5121 keys, 79 against 70 at 8193, 126 against 139 at 16384).
 constexpr int kSelThreads = 1024, kSelBinBits = 13, kSelBins = 1 << kSelBinBits;
 constexpr int kSelList = 1024;     // collected keys
 constexpr int kSelBig = -64;       // histogram code of a bin too full for the list
@@ -250,9 +254,9 @@ constexpr int kSelBig = -64;       // histogram code of a bin too full for the l
 // Few keys: all pairs, 16 tokens a workgroup, so 4096 keys give every CU one.
 // All keys are in LDS and 64 slices of them count for each token, which takes
 // 5.6 us a call at 1000 keys, 6.3 at 4096 and 10.2 at 5000 whatever the keys are
-// (10.6, 35.5 and 43.8 with 64 tokens on four waves). select_budgets takes 12,
-// 11 and 10.7 us, 23 to 43 if many keys are equal; at 5500 keys the ordinary
-// case is level (11.0 and 10.2) and at 6144 it is the faster one (10.5 to 11.7).
+// (10.6, 35.5 and 43.8 with 64 tokens on four waves). select_budgets takes 8 to 10 us
+// at 5121 keys without structure, but 22 to 50 if many are equal: the line lies where
+// all pairs stop being about as fast as the former.
 constexpr int kRankTokens = 16, kRankMax = 5120;
 __global__ __launch_bounds__(kSelThreads) void rank_budgets(const unsigned long long* __restrict__ keys, int n,
                                                             GroupTable tab, int32_t* __restrict__ budget) {
@@ -296,7 +300,9 @@ __global__ __launch_bounds__(kSelThreads) void select_budgets(const unsigned lon
   typedef unsigned long long u64;
   constexpr int kWaves = kSelThreads / kWave, kPer = kSelBins / kSelThreads;
   constexpr unsigned kNone = 0xFFFFFFFFu;  // no token: above every key's upper half
-  __shared__ __attribute__((aligned(16))) int hist[kSelBins + 4];  // and a bin for no token
+  // and a bin for no token in every lane: where the last rows of kSelThreads tokens are
+  // empty, one bin would take all their atomics (35 us at 8193 keys, 15 with these)
+  __shared__ __attribute__((aligned(16))) int hist[kSelBins + kWave];
   __shared__ u64 list_key[kSelList];
   __shared__ int list_tok[kSelList];
   __shared__ unsigned red_lo[kWaves], red_hi[kWaves];
@@ -304,14 +310,16 @@ __global__ __launch_bounds__(kSelThreads) void select_budgets(const unsigned lon
   __shared__ int end_at[kMaxGroups], budget_of[kMaxGroups];
   __shared__ int bin_of[kMaxGroups], before_of[kMaxGroups], count_of[kMaxGroups], slot_of[kMaxGroups];
   __shared__ int slot_off[kMaxGroups + 1], slot_fill[kMaxGroups], slot_before[kMaxGroups], n_slots, n_big;
-  __shared__ int sub_bin, sub_before, sub_count;
-  __shared__ u64 min_of[kWaves], max_of[kWaves];
-  __shared__ u64 thr_key[kMaxGroups];
-  __shared__ int thr_tok[kMaxGroups];
+  __shared__ int bnd_group[kMaxGroups], bnd_range[kMaxGroups], n_bnd;
+  __shared__ int sub_bin[kMaxGroups], sub_before[kMaxGroups], sub_count[kMaxGroups];
+  __shared__ u64 key0[kMaxGroups + 1], key1[kMaxGroups], range_min[kMaxGroups], range_max[kMaxGroups], thr_key[kMaxGroups];
+  __shared__ int key_bits_of[kMaxGroups], tok0[kMaxGroups + 1], tok_bits_of[kMaxGroups], thr_tok[kMaxGroups];
+  __shared__ int range_first[kMaxGroups], range_before[kMaxGroups], range_count[kMaxGroups], range_off[kMaxGroups + 1];
+  __shared__ int n_ranges, n_full, any_key;
   const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
   const int nb = tab.n - 1;  // boundaries
-  // The most keys of one bin that are ranked, at 80 ns each; dividing a bin
-  // takes a few more reads of all keys, 0.2 ns a key and 2 us each.
+  // The most keys of one bin that are ranked. Dividing the bins takes four more
+  // passes over all keys at least, 14 us at 5121 and 70 at 32760.
   const int cap = min(kSelList, max(256, n / 100));
 
   // upper half of the key of token t as it is stored, and of its key_bits
@@ -354,17 +362,33 @@ __global__ __launch_bounds__(kSelThreads) void select_budgets(const unsigned lon
       }
     }
   };
-  // f(key bits, token), for the steps that only the division of full bins takes
-  auto each_again = [&](auto&& f) __attribute__((always_inline)) {
-    constexpr int V = 8;
-#pragma unroll 1
-    for (long t0 = tid; t0 < n; t0 += (long)V * kSelThreads) {
-      u64 k[V];
+  // f(key bits, token), for the steps that only the division of full bins takes:
+  // keys read again, or from hold_keys on held if a thread has few
+  constexpr int V = 8;
+  u64 held[KEYS == V ? V : 1];
+  auto hold_keys = [&]() {
+    if constexpr (KEYS == V) {
 #pragma unroll
-      for (int i = 0; i < V; ++i) k[i] = keys[min(t0 + (long)i * kSelThreads, (long)n - 1)];
+      for (int i = 0; i < V; ++i) held[i] = keys[min(tid + i * kSelThreads, n - 1)];
+#pragma unroll
+      for (int i = 0; i < V; ++i) held[i] = key_bits(held[i]);
+    }
+  };
+  auto each_again = [&](auto&& f) __attribute__((always_inline)) {
+    if constexpr (KEYS == V) {
 #pragma unroll
       for (int i = 0; i < V; ++i)
-        if (t0 + (long)i * kSelThreads < n) f(key_bits(k[i]), (int)(t0 + (long)i * kSelThreads));
+        if (tid + i * kSelThreads < n) f(held[i], tid + i * kSelThreads);
+    } else {
+#pragma unroll 1
+      for (long t0 = tid; t0 < n; t0 += (long)V * kSelThreads) {
+        u64 k[V];
+#pragma unroll
+        for (int i = 0; i < V; ++i) k[i] = keys[min(t0 + (long)i * kSelThreads, (long)n - 1)];
+#pragma unroll
+        for (int i = 0; i < V; ++i)
+          if (t0 + (long)i * kSelThreads < n) f(key_bits(k[i]), (int)(t0 + (long)i * kSelThreads));
+      }
     }
   };
   auto clear_hist = [&]() {
@@ -398,6 +422,7 @@ __global__ __launch_bounds__(kSelThreads) void select_budgets(const unsigned lon
     const u64 k = list_key[i];
     const int t = list_tok[i];
     int r = 0;
+#pragma unroll 8
     for (int j = a; j < b; ++j) r += (list_key[j] < k) | ((list_key[j] == k) & (list_tok[j] < t));
     return r;
   };
@@ -432,7 +457,7 @@ __global__ __launch_bounds__(kSelThreads) void select_budgets(const unsigned lon
   const int shift32 = bits > kSelBinBits ? bits - kSelBinBits : 0;
   const u64 lo = (u64)lo32 << 32;  // the bins in whole keys
   const int shift = shift32 + 32;
-  auto bin32 = [&](unsigned k) { return k == kNone ? (unsigned)kSelBins : (k - lo32) >> shift32; };
+  auto bin32 = [&](unsigned k) { return k == kNone ? (unsigned)(kSelBins + lane) : (k - lo32) >> shift32; };
   // the held keys become their bins: found once, and no lane mask of k == kNone per key stays live
   if constexpr (KEYS > 0) {
 #pragma unroll
@@ -472,6 +497,7 @@ __global__ __launch_bounds__(kSelThreads) void select_budgets(const unsigned lon
     }
   }
   __syncthreads();
+  if (tid < kWave) hist[kSelBins + tid] = kSelBig;  // no token: nothing to write
   if (tid == 0) {  // a slot of the list for every bin with a boundary inside
     int slots = 0, fill = 0, last = -1, big = 0;
     for (int g = 0; g < nb; ++g) {  // ascending ranks: equal bins are adjacent
@@ -491,7 +517,6 @@ __global__ __launch_bounds__(kSelThreads) void select_budgets(const unsigned lon
       }
       last = g;
     }
-    hist[kSelBins] = kSelBig;  // no token: nothing to write
     slot_off[slots] = fill;
     n_slots = slots;
     n_big = big;
@@ -520,124 +545,164 @@ __global__ __launch_bounds__(kSelThreads) void select_budgets(const unsigned lon
   }
   if (!n_big) return;
 
-  struct Range {  // keys k0 .. k0 + 2^ks - 1 of tokens t0 .. t0 + 2^ts - 1
-    u64 k0;
-    int ks, t0, ts;
-  };
-  auto inside = [](const Range& r, u64 k, int t) {
-    return k >= r.k0 && (k - r.k0) >> r.ks == 0 && t >= r.t0 && (t - r.t0) >> r.ts == 0;
-  };
-  auto step_of = [](const Range& r) { return max((r.ks > 0 ? r.ks : r.ts) - kSelBinBits, 0); };
-  // Histogram of a range by key, drawn in to its keys first, or by token if they
-  // are equal: counts of this thread's bins, and the keys before the first of them.
-  auto divide = [&](Range& r, int (&c)[kPer]) __attribute__((always_inline)) -> int {
-    if (r.ks > 0) {
-      u64 a = ~0ull, b = 0;
-      each_again([&](u64 k, int t) {
-        if (!inside(r, k, t)) return;
-        a = min(a, k);
-        b = max(b, k);
-      });
+  hold_keys();
+  // The bins that did not fit. Their boundaries, j = 0 .. n_bnd-1 in order, and the
+  // ranges these lie in, s = 0 .. n_ranges-1 in order: at first the bins, each keys
+  // key0 .. key1 (less than 2^key_bits of them) of every token; among equal keys
+  // (key_bits 0) tokens tok0 .. tok0 + 2^tok_bits - 1. Each round divides all ranges at
+  // once.
+  // Lane j of wave 0 keeps boundary j: new ranges from their boundaries' (id, equal for
+  // boundaries of one range) and, for the first boundary of each, what it is.
+  auto set_ranges = [&](bool bnd, int id, u64 k0, u64 k1, int kb, int t0, int tb, int before, int count) {
+    const int prev = __shfl_up(bnd ? id : -1, 1);
+    const bool lead = bnd && (lane == 0 || prev != id);
+    const u64 leads = __ballot(lead);
+    const int s = __popcll(leads & (2ull << lane) - 1) - 1, ranges = __popcll(leads);
+    if (bnd) bnd_range[lane] = s;
+    if (lane >= ranges && lane <= kMaxGroups) key0[lane] = ~0ull;  // above every key
+    if (lead) {
+      key0[s] = k0;
+      key1[s] = k1;
+      key_bits_of[s] = kb;
+      tok0[s] = t0;
+      tok_bits_of[s] = tb;
+      range_first[s] = lane;
+      range_before[s] = before;
+      range_count[s] = count;
+      range_min[s] = ~0ull;
+      range_max[s] = 0;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    const int c = lane < ranges ? range_count[lane] : 0;
+    int inc = c;
 #pragma unroll
-      for (int o = 32; o > 0; o >>= 1) {
-        a = min(a, (u64)__shfl_xor(a, o));
-        b = max(b, (u64)__shfl_xor(b, o));
-      }
-      if (lane == 0) {
-        min_of[wave] = a;
-        max_of[wave] = b;
-      }
+    for (int o = 1; o < kMaxGroups; o <<= 1) {
+      const int y = __shfl_up(inc, o);
+      if (lane >= o) inc += y;
+    }
+    if (lane <= ranges) range_off[lane] = inc - c;
+    const bool full = __any(c > kSelList / kMaxGroups), by_key = __any(lane < ranges && key_bits_of[lane] > 0);
+    if (lane == 0) {
+      n_ranges = ranges;
+      n_full = full;
+      any_key = by_key;
+    }
+  };
+  if (wave == 0) {
+    const bool big = lane < nb && bin_of[lane] >= 0 && slot_of[lane] < 0;
+    const u64 bigs = __ballot(big);
+    if (lane < kMaxGroups) thr_key[lane] = ~0ull;  // past n_bnd: above every key
+    if (big) bnd_group[__popcll(bigs & (1ull << lane) - 1)] = lane;
+    if (lane == 0) n_bnd = __popcll(bigs);
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    const bool bnd = lane < __popcll(bigs);
+    const int g = bnd ? bnd_group[lane] : 0, bin = bin_of[g];
+    const u64 k0 = lo + ((u64)bin << shift);
+    set_ranges(bnd, bin, k0, k0 + ((1ull << shift) - 1), shift, 0, 32 - __clz(n), before_of[g], count_of[g]);
+  }
+  __syncthreads();
+  // number of the pairs (k[i], t[i]) at or below (key, token), the pairs in ascending
+  // order and past their number above every key; at most 2 top - 1 of them
+  auto pairs_below = [](const u64* k, const int* t, int top, u64 key, int tok) {
+    int j = 0;
+    for (int step = top; step > 0; step >>= 1) {
+      const u64 m = k[j + step - 1];
+      if (m < key || (m == key && t[j + step - 1] <= tok)) j += step;
+    }
+    return j;
+  };
+  // f(range, key bits, token) for the keys inside a range
+  auto each_inside = [&](auto&& f) __attribute__((always_inline)) {
+    const int top = 1 << (31 - __clz(n_ranges));
+    each_again([&](u64 k, int t) {
+      const int s = pairs_below(key0, tok0, top, k, t) - 1;
+      if (s < 0 || k > key1[s] || (key_bits_of[s] == 0 && (t - tok0[s]) >> tok_bits_of[s])) return;
+      f(s, k, t);
+    });
+  };
+  while (true) {
+    if (any_key) {  // draw the key ranges in to their keys
+      each_inside([&](int s, u64 k, int) {
+        // few keys pass the first test, so few atomics meet
+        if (k < __hip_atomic_load(&range_min[s], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP))
+          atomicMin(&range_min[s], k);
+        if (k > __hip_atomic_load(&range_max[s], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP))
+          atomicMax(&range_max[s], k);
+      });
       __syncthreads();
-      for (int w = 0; w < kWaves; ++w) {
-        a = min(a, min_of[w]);
-        b = max(b, max_of[w]);
+      if (tid < n_ranges && key_bits_of[tid] > 0) {
+        const u64 a = range_min[tid], b = range_max[tid];
+        key0[tid] = a;
+        key1[tid] = b;
+        key_bits_of[tid] = b > a ? 64 - __clzll(b - a) : 0;
       }
-      r.k0 = a;
-      r.ks = b > a ? 64 - __clzll(b - a) : 0;
     }
     clear_hist();
-    const int sh = step_of(r);
-    each_again([&](u64 k, int t) {
-      if (inside(r, k, t)) atomicAdd(&hist[r.ks > 0 ? (int)((k - r.k0) >> sh) : (t - r.t0) >> sh], 1);
+    const int bin_bits = kSelBinBits - (n_ranges > 1 ? 32 - __clz(n_ranges - 1) : 0);  // bins of a range
+    auto step_of = [&](int s) { return max((key_bits_of[s] > 0 ? key_bits_of[s] : tok_bits_of[s]) - bin_bits, 0); };
+    each_inside([&](int s, u64 k, int t) {
+      const int b = key_bits_of[s] > 0 ? (int)((k - key0[s]) >> step_of(s)) : (t - tok0[s]) >> step_of(s);
+      atomicAdd(&hist[(s << bin_bits) + b], 1);
     });
-    return scan_bins(c);
-  };
-  Range bin = {};
-  int bin_c[kPer] = {}, bin_p = 0;
-  for (int g = 0; g < nb; ++g) {  // the element of each boundary inside a bin that did not fit
-    if (bin_of[g] < 0 || slot_of[g] >= 0) continue;
-    const int e = end_at[g];
-    const bool known = g > 0 && bin_of[g - 1] == bin_of[g];  // divided for the boundary before
-    Range r = known ? bin : Range{lo + ((u64)bin_of[g] << shift), shift, 0, 32 - __clz(n)};
-    int before = before_of[g], count;
-    bool whole = true;  // r is still the whole bin
-    do {
-      int c[kPer], p;
-      if (whole && known) {
-        p = bin_p;
+    int c[kPer];
+    const int p = scan_bins(c), s = tid * kPer >> bin_bits;  // this thread's bins are of one range
+    int sum = 0;
 #pragma unroll
-        for (int i = 0; i < kPer; ++i) c[i] = bin_c[i];
-      } else {
-        p = divide(r, c);
-        if (whole) {
-          bin = r;
-          bin_p = p;
-#pragma unroll
-          for (int i = 0; i < kPer; ++i) bin_c[i] = c[i];
-        }
-      }
-      p += before;
+    for (int i = 0; i < kPer; ++i) sum += c[i];
+    for (int j = s < n_ranges ? range_first[s] : n_bnd; j < n_bnd && bnd_range[j] == s; ++j) {
+      int q = range_before[s] + p - range_off[s];
+      const int e = end_at[bnd_group[j]];
+      if (e < q || e - q >= sum) continue;
 #pragma unroll
       for (int i = 0; i < kPer; ++i) {
-        if (e >= p && e - p < c[i]) {
-          sub_bin = tid * kPer + i;
-          sub_before = p;
-          sub_count = c[i];
+        if (e >= q && e - q < c[i]) {
+          sub_bin[j] = (tid * kPer + i) - (s << bin_bits);
+          sub_before[j] = q;
+          sub_count[j] = c[i];
         }
-        p += c[i];
+        q += c[i];
       }
-      __syncthreads();
-      const int sh = step_of(r);
-      if (r.ks > 0) {
-        r.k0 += (u64)sub_bin << sh;
-        r.ks = sh;
-      } else {
-        r.t0 += sub_bin << sh;
-        r.ts = sh;
-      }
-      before = sub_before;
-      count = sub_count;
-      whole = false;
-      __syncthreads();  // sub_* are read
-    } while (count > cap);
-    __syncthreads();  // the list is no longer read
-    if (tid == 0) slot_fill[0] = 0;
+    }
     __syncthreads();
-    each_again([&](u64 k, int t) {
-      if (inside(r, k, t)) {
-        const int at = atomicAdd(&slot_fill[0], 1);
-        list_key[at] = k;
-        list_tok[at] = t;
-      }
-    });
+    if (wave == 0) {
+      const bool bnd = lane < n_bnd;
+      const int j = bnd ? lane : 0, r = bnd_range[j], b = sub_bin[j], sh = step_of(r), kb = key_bits_of[r];
+      const u64 k0 = kb > 0 ? key0[r] + ((u64)b << sh) : key0[r];
+      const u64 k1 = kb > 0 ? min(key1[r], k0 + ((1ull << sh) - 1)) : key1[r];
+      const int t0 = kb > 0 ? 0 : tok0[r] + (b << sh), tb = kb > 0 ? 32 - __clz(n) : sh;
+      const int before = sub_before[j], count = sub_count[j];
+      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");  // read before the ranges are replaced
+      set_ranges(bnd, (r << kSelBinBits) + b, k0, k1, kb > 0 ? sh : 0, t0, tb, before, count);
+    }
     __syncthreads();
-    for (int i = tid; i < count; i += kSelThreads)
-      if (before + rank_in(i, 0, count) == e) {
-        thr_key[g] = list_key[i];
-        thr_tok[g] = list_tok[i];
+    if (!n_full) break;
+  }
+  // all ranges fit the list: the element (key, token) of each boundary
+  if (tid < kMaxGroups) slot_fill[tid] = 0;
+  __syncthreads();
+  each_inside([&](int s, u64 k, int t) {
+    const int at = range_off[s] + atomicAdd(&slot_fill[s], 1);
+    list_key[at] = k;
+    list_tok[at] = t;
+  });
+  __syncthreads();
+  for (int i = tid; i < range_off[n_ranges]; i += kSelThreads) {
+    int s = 0;
+    while (i >= range_off[s + 1]) ++s;
+    const int r = range_before[s] + rank_in(i, range_off[s], range_off[s + 1]);
+    for (int j = 0; j < n_bnd; ++j)
+      if (end_at[bnd_group[j]] == r) {
+        thr_key[j] = list_key[i];
+        thr_tok[j] = list_tok[i];
       }
   }
   __syncthreads();
+  const int top_bnd = 1 << (31 - __clz(n_bnd));
   each_again([&](u64 k, int t) {
-    const int bin = (int)((k - lo) >> shift);
-    int before = -1;  // keys before the bin, if it is one that did not fit
-    for (int g = 0; g < nb; ++g)
-      if (bin_of[g] == bin && slot_of[g] < 0) before = before_of[g];
-    if (before < 0) return;
-    int group = 0;
-    for (int g = 0; g < nb; ++g)
-      group += bin_of[g] == bin ? k > thr_key[g] || (k == thr_key[g] && t >= thr_tok[g]) : end_at[g] <= before;
-    budget[t] = budget_of[group];
+    const int bin = (int)((k - lo) >> shift), j = pairs_below(thr_key, thr_tok, top_bnd, k, t);
+    // behind a boundary of the token's bin, or before its first one; else the bin is none of these
+    if (j > 0 && bin_of[bnd_group[j - 1]] == bin) budget[t] = budget_of[bnd_group[j - 1] + 1];
+    else if (j < n_bnd && bin_of[bnd_group[j]] == bin) budget[t] = budget_of[bnd_group[j]];
   });
 }
 

@@ -152,12 +152,23 @@ def _keys(pattern, n, rng):
         return k - 64
     if pattern == "lognormal":
         return np.exp(4 * rng.standard_normal(n))
+    if pattern == "levels":  # most boundaries among equal keys, each level a bin of its own
+        return rng.integers(1, 17, n).astype(np.float64)
+    if pattern == "levels_and_outlier":  # several levels share a bin, and each boundary a level with others
+        k = 1.0 + rng.integers(0, 6, n) * 2.0 ** -40
+        k[rng.integers(0, n)] = 1e300
+        return k
+    if pattern == "descending":  # within the bin of an outlier, so every key is a new minimum of it
+        k = 1.0 + 1e-9 * np.arange(n, 0, -1)
+        k[0] = 1e300
+        return k
     return k
 
 
 # tokens around a wave, the workgroup, the list, the register-resident limit (32768)
 @pytest.mark.parametrize("n", [1, 2, 17, 63, 1025, 4097, 5120, 5121, 8193, 32768, 32769, 75601])
-@pytest.mark.parametrize("pattern", ["chi2", "equal", "two_values", "outliers", "many_nan", "negative", "lognormal"])
+@pytest.mark.parametrize("pattern", ["chi2", "equal", "two_values", "outliers", "many_nan", "negative", "lognormal",
+                                     "levels", "levels_and_outlier", "descending"])
 @pytest.mark.parametrize("n_groups", [1, 3, 16])
 def test_assign_budgets_by_key_edges(n, pattern, n_groups):
     rng = np.random.default_rng(n * 31 + n_groups)
