@@ -294,15 +294,41 @@ __device__ __forceinline__ void row_gemm_tile(const RowGemm& g, int tm, int tn, 
     };
     issue_b(Int<0>{}, 0);
     issue_a(Int<0>{}, 0);
-    issue_b(Int<1>{}, min(1, nk - 1) * BK);
-    __builtin_amdgcn_s_waitcnt(waitcnt_vm(LOADS_B));
-    barrier();
-    if (__builtin_amdgcn_readfirstlane(wave) >= 4) {
+    if (nk <= 2) {
+      // One or two steps, whose tiles all fit: every wave reads and multiplies as it
+      // can. The loop's slots would mostly be spent alone here, and its loads past the
+      // last step be more than the others (8190 x 64 -> 5120 30.3 us with the loop, 28.2 so).
+      if (nk == 2) {
+        issue_b(Int<1>{}, BK);
+        issue_a(Int<1>{}, BK);
+        __builtin_amdgcn_s_waitcnt(waitcnt_vm(LOADS));
+      } else {
+        __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
+      }
       barrier();
-      steps(std::true_type{});
+      read(Int<0>{}, 0);
+      mfmas();
+      read(Int<0>{}, 1);
+      mfmas();
+      if (nk == 2) {
+        __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
+        barrier();
+        read(Int<1>{}, 0);
+        mfmas();
+        read(Int<1>{}, 1);
+        mfmas();
+      }
     } else {
-      steps(std::false_type{});
+      issue_b(Int<1>{}, BK);
+      __builtin_amdgcn_s_waitcnt(waitcnt_vm(LOADS_B));
       barrier();
+      if (__builtin_amdgcn_readfirstlane(wave) >= 4) {
+        barrier();
+        steps(std::true_type{});
+      } else {
+        steps(std::false_type{});
+        barrier();
+      }
     }
   } else {
     // Ring K loop: step k's stage has landed and everyone is done with step
@@ -373,10 +399,13 @@ __device__ __forceinline__ void row_gemm_tile(const RowGemm& g, int tm, int tn, 
   // one. A wave waits for a load by counting its outstanding memory
   // accesses, stores included, so a load behind a store would also wait for
   // that store (measured: the output projection 2-9% faster this way).
-  constexpr int TNP = TN + 4;         // padded staging row, floats
+  // Each lane fills whole entries of the row tables (one lane of the 16-row tiles'
+  // four for each row, every row tile by itself, took 63 VALU instructions more) and the
+  // staging has no bank conflicts: 8190 x 64 -> 5120 28.2 -> 26.3 us, 8190 x 512 -> 5120
+  // 52.0 -> 50.5.
   constexpr int QPR = TN / 4;         // 4-column groups per row
   constexpr int NT = QPR / 2;         // read-back passes of the wave per block
-  constexpr int REGION = 32 * TNP * 4 + TM * (8 + 4);
+  constexpr int REGION = 32 * TN * 4 + TM * (8 + 4);
   constexpr int PER = TL::PING ? 2 : (TL::WAVES + RING - 1) / RING;  // waves per array
   static_assert(PER * REGION <= TL::ARRAY * 2 && PER * TL::ARRAYS >= TL::WAVES, "epilogue staging must fit");
   static_assert(QPR % 2 == 0, "the wave covers whole rows in each read-back pass");
@@ -386,15 +415,20 @@ __device__ __forceinline__ void row_gemm_tile(const RowGemm& g, int tm, int tn, 
   for (int i = 1; i < TL::ARRAYS; ++i)
     if (wave / PER == i) staging = lds.p[i];
   char* region = reinterpret_cast<char*>(staging) + (wave % PER) * REGION;
-  float* blk = reinterpret_cast<float*>(region);
+  f32x4* blk = reinterpret_cast<f32x4*>(region);
+  // 4-column group q of row r sits at q ^ f(r): the writes (16 rows, 4 groups) and
+  // the reads (whole rows) that are served together hit disjoint banks
+  auto slot = [](int r, int q) { return r * QPR + (q ^ (QPR == 16 ? r & 15 : QPR == 8 ? (r >> 1) & 7 : r & 7)); };
+  static_assert(QPR == 8 || QPR == 16 || QPR == 24, "staging rows of 32, 64 or 96 columns");
   // per block i, row r: output element offset and target (0: C, 1: C2, -1: none)
-  long* row_off = reinterpret_cast<long*>(region + 32 * TNP * 4);
-  int* row_buf = reinterpret_cast<int*>(region + 32 * TNP * 4 + TM * 8);
+  long* row_off = reinterpret_cast<long*>(region + 32 * TN * 4);
+  int* row_buf = reinterpret_cast<int*>(region + 32 * TN * 4 + TM * 8);
   const int32_t* c_rows = oz.c_rows;
   const bool rope = ROPE && g.rope_cs && ((g.rope_outs >> z) & 1);
   const int col0 = tn * BN + wn * TN;  // first output column of the wave tile
   const int m0 = tm * BM + wm * TM + l16;  // the lane's row in row tile 0
-  int crow[MI];
+  constexpr int RT = (TM + 63) / 64;       // rows of the tables per lane
+  int crow[RT];
   float rs[MI];
   RopeRow rr[MI];
   // Loads under a lane condition would each be waited for inside their
@@ -402,11 +436,14 @@ __device__ __forceinline__ void row_gemm_tile(const RowGemm& g, int tm, int tn, 
   // address unconditionally (row M-1 for the rows past M) and its value is
   // selected afterwards.
 #pragma unroll
+  for (int t = 0; t < RT; ++t) {
+    const int m = tm * BM + wm * TM + t * 64 + lane;
+    const int cr = c_rows ? c_rows[min(m, g.M - 1)] : m;
+    crow[t] = m < g.M ? cr : -1;
+  }
+#pragma unroll
   for (int i = 0; i < MI; ++i) {
-    const int m = m0 + i * 16;
-    const int mc = min(m, g.M - 1);
-    const int cr = c_rows ? c_rows[mc] : m;
-    crow[i] = m < g.M ? cr : -1;
+    const int mc = min(m0 + i * 16, g.M - 1);
     rs[i] = g.row_scale ? g.row_scale[mc] : 1.f;
     if constexpr (!TL::PING) {
       if (g.rms) {
@@ -419,17 +456,17 @@ __device__ __forceinline__ void row_gemm_tile(const RowGemm& g, int tm, int tn, 
     if (rope) rr[i] = rope_row(g, mc);
   }
 #pragma unroll
-  for (int i = 0; i < MI; ++i) {
+  for (int t = 0; t < RT; ++t) {
     int buf = -1;
     long obase = 0;
-    if (crow[i] >= 0 && crow[i] < oz.c_limit) {
-      const bool second = oz.C2 && crow[i] >= oz.c_split;  // rows past the split go to C2
+    if (crow[t] >= 0 && crow[t] < oz.c_limit) {
+      const bool second = oz.C2 && crow[t] >= oz.c_split;  // rows past the split go to C2
       buf = second ? 1 : 0;
-      obase = (long)(second ? crow[i] - oz.c_split : crow[i]) * g.ldc;
+      obase = (long)(second ? crow[t] - oz.c_split : crow[t]) * g.ldc;
     }
-    if (grp == 0) {
-      row_off[i * 16 + l16] = obase;
-      row_buf[i * 16 + l16] = buf;
+    if (TM % 64 == 0 || lane < TM) {
+      row_off[t * 64 + lane] = obase;
+      row_buf[t * 64 + lane] = buf;
     }
   }
   __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");  // the row tables are visible
@@ -486,7 +523,7 @@ __device__ __forceinline__ void row_gemm_tile(const RowGemm& g, int tm, int tn, 
 #pragma unroll
           for (int u = 0; u < 4; ++u) v[u] = gelu_tanh(v[u]);
         }
-        *reinterpret_cast<f32x4*>(blk + (h * 16 + l16) * TNP + j * 16 + grp * 4) = v;
+        blk[slot(h * 16 + l16, j * 4 + grp)] = v;
       }
     }
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
@@ -495,7 +532,7 @@ __device__ __forceinline__ void row_gemm_tile(const RowGemm& g, int tm, int tn, 
     for (int t = 0; t < NT; ++t) {
       const int f = lane + 64 * t;
       const int r = f / QPR, cq = f - r * QPR;
-      f32x4 v = *reinterpret_cast<const f32x4*>(blk + r * TNP + cq * 4);
+      f32x4 v = blk[slot(r, cq)];
       if constexpr (EPI == kEpiF32) {
         ov[i][t] = v;
       } else {
