@@ -236,9 +236,10 @@ __device__ __forceinline__ void row_gemm_tile(const RowGemm& g, int tm, int tn, 
   };
 
   const int nk = g.K / BK;
-  float sq[MI];  // ring, g.rms: sums of squares of the lane's A rows
-#pragma unroll
-  for (int i = 0; i < MI; ++i) sq[i] = 0.f;
+  // ring, g.rms: sums of squares of the lane's A rows, eight each, so that their chains of
+  // roundings are as short as those of row_rms_scale (the fp32 velocities of a head at
+  // d = 5120 are 4.5e-7 off the exact product with either; 4.9e-7 with one sum a row)
+  float sq[MI][2][4] = {};
   if constexpr (TL::PING) {
     // Ping-pong K loop. Waves w and w + 4 share a SIMD; the waves of one half
     // read fragments and issue tile loads while the other half's run MFMAs and
@@ -338,14 +339,14 @@ __device__ __forceinline__ void row_gemm_tile(const RowGemm& g, int tm, int tn, 
     // row l16 of each row tile per fragment (a launch of few tiles waits for its
     // chain of steps, not for these; a kernel of its own for them costs 4 us:
     // an iteration of three blocks, 500 rows at d = 256, 241 -> 220 us).
-    auto squares = [&]() __attribute__((always_inline)) {
+    auto squares = [&](int half) __attribute__((always_inline)) {
       if (!g.rms) return;
 #pragma unroll
       for (int i = 0; i < MI; ++i)
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
           const bf16x2 pair = {af[i][2 * u], af[i][2 * u + 1]};
-          sq[i] = __builtin_amdgcn_fdot2_f32_bf16(pair, pair, sq[i], false);
+          sq[i][half][u] = __builtin_amdgcn_fdot2_f32_bf16(pair, pair, sq[i][half][u], false);
         }
     };
     auto step = [&](auto uc, int k) __attribute__((always_inline)) {
@@ -356,10 +357,10 @@ __device__ __forceinline__ void row_gemm_tile(const RowGemm& g, int tm, int tn, 
       issue_a(Next{}, min(k + RING - 1, nk - 1) * BK);
       issue_b(Next{}, min(k + RING - 1, nk - 1) * BK);
       mfmas();
-      squares();
+      squares(0);
       read(uc, 1);
       mfmas();
-      squares();
+      squares(1);
       read_done();
     };
     static_for<0, RING - 1>([&](auto uc) {
@@ -447,7 +448,9 @@ __device__ __forceinline__ void row_gemm_tile(const RowGemm& g, int tm, int tn, 
     rs[i] = g.row_scale ? g.row_scale[mc] : 1.f;
     if constexpr (!TL::PING) {
       if (g.rms) {
-        float t = sq[i] + __shfl_xor(sq[i], 16);
+        float t = ((sq[i][0][0] + sq[i][0][1]) + (sq[i][0][2] + sq[i][0][3])) +
+                  ((sq[i][1][0] + sq[i][1][1]) + (sq[i][1][2] + sq[i][1][3]));
+        t += __shfl_xor(t, 16);
         t += __shfl_xor(t, 32);
         rs[i] = 1.0f / sqrtf(t / (float)g.K + g.rms_eps);
       }

@@ -348,6 +348,30 @@ def test_iteration_small_tilings_form_the_rms_factors(rows, heads, ffn, channels
         assert float((got.float() - want.float()).norm() / want.float().norm()) < 2.0 ** -7
 
 
+@pytest.mark.parametrize("rows,heads", [(80, 2), (300, 40)])
+def test_rms_factors_of_the_small_tilings_against_float64(rows, heads):
+    """The fp32 velocities of a stack without layers, rms(h) W^T: per row, the factor by which they miss the float64
+    product of the same h is on average no larger than with the factors of hsa_row_rms_scale."""
+    from paper_2605_06892_amd import stack
+
+    g = torch.Generator(device=DEV).manual_seed(rows)
+    bf, d, c = torch.bfloat16, heads * 128, 64
+    b = stack.StackBuffers.allocate(rows, c, 0, heads, 128, bf)
+    b.x, b.v_hat = torch.randn(rows, c, generator=g, device=DEV), torch.zeros(rows, c, device=DEV)
+    b.budget.fill_(4)
+    b.w_embed = (torch.randn(d, c, generator=g, device=DEV) * c ** -0.5).to(bf)
+    b.w_head = (torch.randn(c, d, generator=g, device=DEV) * d ** -0.5).to(bf)
+    stack.iteration(b, 4, 1, np.array([1, 0.75, 0.5, 0.25, 0], np.float32))
+    h = b.h[:rows].double()
+    want = h * torch.rsqrt((h * h).mean(1, keepdim=True) + 1e-6) @ b.w_head.double().t()
+    scale, separate = torch.empty(rows, device=DEV), torch.empty(rows, c, device=DEV)
+    H.hsa_row_rms_scale(b.h, rows, scale)
+    H.hsa_linear(b.h, rows, b.w_head, separate, row_scale=scale)
+    miss = [float(((v.double() * want).sum(1) / (want * want).sum(1) - 1).abs().mean()) for v in (b.v_hat, separate)]
+    # a quarter for chance: means over some hundred rows of roundings that both kernels draw alike
+    assert miss[0] < 1.25 * miss[1] < 2.0 ** -22
+
+
 @pytest.mark.parametrize("pinned", [True, False])
 @pytest.mark.parametrize("slot", [0, 3, 7])
 @pytest.mark.parametrize("n", [1, 5000, 32760])
