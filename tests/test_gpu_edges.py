@@ -273,15 +273,19 @@ def test_qkv_bf16_small_tilings_scatter(m, d):
     assert bool((kc[skipped] == 7.0).all()) and bool((vc[skipped] == 7.0).all())
 
 
-# queries around the 16-query tiles of a wave and the 256 of a workgroup, rows around the 16-key tiles,
-# the 32-key blocks and the 96-row LDS tiles
+# queries around the small kernel's 16 of a workgroup and the large one's 32 of a wave and 256 of a
+# workgroup, rows around the 16-key tiles, the 32-key blocks and the large kernel's 96-row LDS tiles; the
+# launcher gives all but (700, 77, 12) and, with a scratch, (40, 3000, 1) to the small kernel
 @pytest.mark.parametrize("n_q,n_kv,heads,dh", [
     (1, 1, 1, 128), (15, 15, 2, 64), (16, 17, 2, 128), (17, 31, 1, 128), (33, 95, 2, 128), (255, 97, 1, 64),
     (257, 193, 3, 128), (300, 400, 2, 64), (500, 1000, 2, 128), (40, 3000, 1, 128), (700, 77, 12, 128),
 ])
 @pytest.mark.parametrize("spread", [1.0, 12.0])
-def test_attention_bf16_edges(n_q, n_kv, heads, dh, spread):
+@pytest.mark.parametrize("kernel", ["launcher", "large"])
+def test_attention_bf16_edges(n_q, n_kv, heads, dh, spread, kernel, monkeypatch):
     """With and without a scratch for key parts; spread 12: the reference maximum has to be raised."""
+    if kernel == "large":
+        monkeypatch.setenv("HSA_ATTN_WAVES", "8")
     g = _gen(n_q * 1000 + n_kv)
     d = heads * dh
     q, k, v = ((torch.randn(n, d, generator=g) * s).to(torch.bfloat16)

@@ -316,6 +316,15 @@ def test_zero_active_rows_is_a_no_op():
 # attention
 # ---------------------------------------------------------------------------
 
+@pytest.fixture(params=["launcher", "large"])
+def bf16_attention(request, monkeypatch):
+    """The launcher's own choice of the bf16 kernel (the small one for most shapes here), and the large one, which
+    a forced workgroup shape always takes."""
+    if request.param == "large":
+        monkeypatch.setenv("HSA_ATTN_WAVES", "8")
+    return request.param
+
+
 ATTN_CASES = [
     # dtype, N keys, active queries, heads, head_dim
     ("bf16", 1000, 300, 2, 128),
@@ -325,9 +334,9 @@ ATTN_CASES = [
     ("bf16", 64, 128, 2, 128),
     ("bf16", 4109, 4096, 32, 128),   # two 32-query sub-tiles per wave
     ("bf16", 2000, 2048, 64, 64),    # idem, head_dim 64
-    # key counts around the 96-row key tile and the 3-tile loop unroll: one block, one tile,
-    # one tile + 1 row, two blocks of a second tile, three tiles, three tiles + 1 row, a
-    # ragged 31-row last block
+    # key counts around the large kernel's 96-row key tile and its 3-tile loop unroll: one
+    # block, one tile, one tile + 1 row, two blocks of a second tile, three tiles, three tiles
+    # + 1 row, a ragged 31-row last block
     ("bf16", 32, 7, 1, 128),
     ("bf16", 96, 40, 1, 128),
     ("bf16", 97, 40, 1, 64),
@@ -342,8 +351,10 @@ ATTN_CASES = [
 
 
 @pytest.mark.parametrize("case", ATTN_CASES, ids=lambda c: "_".join(map(str, c)))
-def test_attention_core(case):
+def test_attention_core(case, bf16_attention):
     dtype, N, nA, heads, dh = case
+    if dtype == "f32" and bf16_attention == "large":
+        pytest.skip("one fp32 kernel")
     d = heads * dh
     rng = np.random.default_rng(N + nA)
     q_np, k_np, v_np = (rng.standard_normal((r, d)).astype(np.float32) for r in (nA, N, N))
@@ -358,7 +369,7 @@ def test_attention_core(case):
     assert np.all(np.isfinite(host(o)))
 
 
-def test_attention_softmax_is_shift_safe():
+def test_attention_softmax_is_shift_safe(bf16_attention):
     """Large scores (|s| ~ 1e3) must not overflow the online softmax."""
     N, nA, heads, dh = 500, 130, 1, 128
     rng = np.random.default_rng(2)
@@ -486,11 +497,11 @@ def test_attention_key_parts_shift_safe(monkeypatch):
     assert rel_inf(o, ref) <= TOL["bf16"]
 
 
-def test_attention_key_parts_auto_and_minimum_workspace():
+def test_attention_key_parts_auto_and_minimum_workspace(bf16_attention):
     """A launch of few workgroups (one head, 256 queries, 4096 keys) splits
     on its own with the key-part workspace and matches the oracle; with the
-    minimum workspace it does not split and equals hsa_attention_core bit for
-    bit."""
+    minimum workspace it does not split (the launcher then takes the small kernel)
+    and equals hsa_attention_core bit for bit."""
     N, nA, heads, dh = 4096, 256, 1, 128
     rng = np.random.default_rng(11)
     q_np, k_np, v_np = (synth.to_bf16_values(rng.standard_normal((r, dh)).astype(np.float32)) for r in (nA, N, N))
