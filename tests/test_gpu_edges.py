@@ -165,8 +165,10 @@ def _keys(pattern, n, rng):
     return k
 
 
-# tokens around a wave, the workgroup, the list, the register-resident limit (32768)
-@pytest.mark.parametrize("n", [1, 2, 17, 63, 1025, 4097, 5120, 5121, 8193, 32768, 32769, 75601])
+# tokens around a wave, the workgroup, the list, the last of the all-pairs kernel (5120) and of the selection
+# with 8, 32 and 80 keys a thread in registers (8192, 32768, 81920), and beyond, where they are read again
+@pytest.mark.parametrize("n", [1, 2, 17, 63, 1025, 4097, 5120, 5121, 8192, 8193, 32768, 32769, 75601, 81920, 81921,
+                               100003])
 @pytest.mark.parametrize("pattern", ["chi2", "equal", "two_values", "outliers", "many_nan", "negative", "lognormal",
                                      "levels", "levels_and_outlier", "descending"])
 @pytest.mark.parametrize("n_groups", [1, 3, 16])
