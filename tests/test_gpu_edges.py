@@ -354,6 +354,50 @@ def test_iteration_small_tilings_form_the_rms_factors(rows, heads, ffn, channels
         assert float((got.float() - want.float()).norm() / want.float().norm()) < 2.0 ** -7
 
 
+# 1000 tokens, the first n_lead of them below the full budget: products of 1000 and 1000 - n_lead rows on the
+# 64 x 64 (2 heads) and the 64 x 64, 64 x 128 and 128 x 128 tilings (6 heads), and, but for 1000 queries of 6 heads,
+# the small attention kernel, whose waves take the 32-key blocks in turn; extra moves the split into other waves' shares
+@pytest.mark.parametrize("heads", [2, 6])
+@pytest.mark.parametrize("n_lead,extra", [(0, 0), (100, 0), (100, 64), (500, 0), (500, 192), (750, 0)])
+def test_prefix_cache_on_the_small_kernels(heads, n_lead, extra):
+    """Two bf16 layers with RoPE: keys and values split into a cache prefix and a fresh tail, in the products' stores
+    and in the attention's loads, give the bits that a cache of all rows gives; and the first layer's cache
+    holds the rotated keys and the values of its input."""
+    from paper_2605_06892_amd import stack
+
+    n, c, d, bf, T = 1000, 64, heads * 128, torch.bfloat16, 8
+    sigmas = np.linspace(1, 0, T + 1).astype(np.float32)
+    runs = []
+    for n_cached in (None, stack.prefix_rows(n_lead, n) + extra):
+        g = torch.Generator(device=DEV).manual_seed(heads + n_lead)
+        rn = lambda o, i: (torch.randn(o, i, generator=g, device=DEV) * i ** -0.5).to(bf)  # noqa: E731
+        b = stack.StackBuffers.allocate(n, c, 2, heads, 128, bf, n_cached=n_cached)
+        b.x, b.v_hat = torch.randn(n, c, generator=g, device=DEV), torch.zeros(n, c, device=DEV)
+        b.w_embed, b.w_head = rn(d, c), rn(c, d)
+        b.layers = [tuple(rn(d, d) for _ in range(4)) for _ in range(2)]
+        b.budget.fill_(T)
+        b.budget[:n_lead] = torch.tensor([2, 4], dtype=torch.int32, device=DEV)[torch.arange(n_lead, device=DEV) % 2]
+        b.enable_rope((2, 20, 25))
+        x0 = b.x.to(bf).float()
+        # all tokens, those of the full budget, and these with the half budget's
+        assert [stack.iteration(b, T, i, sigmas)[0] for i in range(3)] == [n, n - n_lead, n - n_lead // 2 - n_lead % 2]
+        runs.append(b)
+    full, pre = runs
+    rows = pre.n_cached
+    assert torch.equal(full.x, pre.x) and torch.equal(full.v_hat, pre.v_hat)
+    for (k0, v0), (k1, v1) in zip(full.caches, pre.caches):
+        assert torch.equal(k0[:rows], k1[:rows]) and torch.equal(v0[:rows], v1[:rows])
+    assert torch.equal(full.caches[-1][0][rows:], pre.k_tail) and torch.equal(full.caches[-1][1][rows:], pre.v_tail)
+    # tokens of budget 2 were active in the first iteration only, with x0 as their input
+    first = torch.arange(0, n_lead, 2, device=DEV)
+    h = (x0[first] @ full.w_embed.float().t()).to(bf).float()
+    normed = h * torch.rsqrt((h * h).mean(1, keepdim=True) + 1e-6)
+    want = normed @ full.layers[0][2].float().t()
+    got = pre.caches[0][1][first].float()
+    # two roundings to bf16, of h (summed in another order) and of the value
+    assert got.numel() == 0 or float((got - want).norm() / want.norm()) < 2.0 ** -8
+
+
 @pytest.mark.parametrize("rows,heads", [(80, 2), (300, 40)])
 def test_rms_factors_of_the_small_tilings_against_float64(rows, heads):
     """The fp32 velocities of a stack without layers, rms(h) W^T: per row, the factor by which they miss the float64
