@@ -28,7 +28,7 @@ def _attend64(q, k, v, heads):
 
 
 # queries around the 16- and 32-query workgroups, rows around the 32-key blocks and the 8 waves'
-# share of 256; (80, 16 heads) launches 32-query workgroups on 256 compute units, the others 16
+# share of 256; the launches of 16 heads take 32-query workgroups on 256 compute units, the others 16
 @pytest.mark.parametrize("n_q,n_kv,heads,dh", [
     (1, 1, 1, 64), (15, 31, 2, 64), (16, 32, 1, 128), (17, 33, 2, 128), (31, 255, 3, 64), (33, 257, 2, 64),
     (33, 289, 2, 128), (300, 77, 16, 64), (300, 290, 16, 128), (289, 512, 16, 64),
@@ -202,8 +202,8 @@ def test_assign_budgets_by_key_at_the_end_of_an_allocation(n):
     assert np.array_equal(out.cpu().numpy(), _ranked_budgets(keys, groups))
 
 
-# tokens around the 64 of a workgroup, channels around the 64 of a chunk and off the 16-byte path
-@pytest.mark.parametrize("n", [1, 63, 64, 65, 1000])
+# tokens around the 32 of a workgroup, channels around the 64 of a chunk and off the 16-byte path
+@pytest.mark.parametrize("n", [1, 31, 32, 33, 63, 64, 65, 1000])
 @pytest.mark.parametrize("channels", [4, 16, 62, 64, 68, 200])
 def test_l1_rel_edges(n, channels):
     rng = np.random.default_rng(n + channels)
@@ -229,11 +229,12 @@ def test_l1_rel_edges(n, channels):
 
 
 # one shape per tiling of the bf16 product on 256 compute units (64 x 64, 64 x 128, 128 x 128, 256 x 128,
-# 256 x 192, 256 x 256, 256 x 256 with a split last round), all with ragged last rows and columns
+# 256 x 192, 256 x 256, 256 x 256 with a split last round), all with ragged last rows and columns, for the
+# fp32 output too
 GEMM_SHAPES = [(65, 68), (1000, 1532), (2000, 1532), (4090, 1532), (8190, 1532), (2590, 5116), (8190, 5116)]
 
 
-# K steps 1 .. 8: the ends of the loops unrolled by 4 and 6
+# K steps 1 .. 8: the large tilings' one and two steps without a loop, the ends of the loops unrolled by 4 and 6
 @pytest.mark.parametrize("m,n", GEMM_SHAPES)
 @pytest.mark.parametrize("steps", [1, 2, 3, 4, 5, 6, 7, 8])
 def test_linear_bf16_edges(m, n, steps):
@@ -255,9 +256,10 @@ def test_linear_bf16_edges(m, n, steps):
     assert bool((f[m] == 7.0).all())
 
 
-@pytest.mark.parametrize("m,d", [(70, 64), (300, 256), (700, 1536), (2000, 1536)])
+# 64 x 64, the same, 64 x 128, 128 x 128 and, one of the large tilings, 256 x 192 on 256 compute units
+@pytest.mark.parametrize("m,d", [(70, 64), (300, 256), (250, 1536), (700, 1536), (2000, 1536)])
 def test_qkv_bf16_small_tilings_scatter(m, d):
-    """Gathered rows in, scattered rows out, on the small tilings; other cache rows untouched."""
+    """Gathered rows in, scattered rows out, on the small tilings (and a large one); other cache rows untouched."""
     g = torch.Generator(device=DEV).manual_seed(m + d)
     n = 2 * m + 5
     x = torch.randn(n, d, generator=g, device=DEV).to(torch.bfloat16)
@@ -361,8 +363,8 @@ def test_iteration_small_tilings_form_the_rms_factors(rows, heads, ffn, channels
 @pytest.mark.parametrize("n_lead,extra", [(0, 0), (100, 0), (100, 64), (500, 0), (500, 192), (750, 0)])
 def test_prefix_cache_on_the_small_kernels(heads, n_lead, extra):
     """Two bf16 layers with RoPE: keys and values split into a cache prefix and a fresh tail, in the products' stores
-    and in the attention's loads, give the bits that a cache of all rows gives; and the first layer's cache
-    holds the rotated keys and the values of its input."""
+    and in the attention's loads, give the bits that a cache of all rows gives; and the first layer's
+    cached values are those of its input."""
     from paper_2605_06892_amd import stack
 
     n, c, d, bf, T = 1000, 64, heads * 128, torch.bfloat16, 8
