@@ -228,6 +228,22 @@ def test_l1_rel_edges(n, channels):
     assert torch.count_nonzero(ta) == 0 and torch.equal(tp, tv)
 
 
+def test_l1_rel_of_the_most_tokens():
+    """2^31 - 1 tokens of 4 channels (86 GB): more threads than one launch of the vector kernel may have."""
+    n = 2 ** 31 - 1
+    if torch.cuda.mem_get_info()[0] < 100 << 30:
+        pytest.skip("needs 100 GB of device memory")
+    v, p = torch.empty(n, 4, device=DEV), torch.empty(n, 4, device=DEV)
+    acc = torch.empty(n, dtype=torch.float64, device=DEV)
+    rows = [0, n // 2, n - 1]
+    for r in rows:
+        v[r], p[r], acc[r] = 2.0, 1.0, 0.25
+    H.hsa_l1_rel_accumulate(v, p, acc, False)
+    assert acc[rows].tolist() == [0.75] * 3 and bool((p[rows] == 2.0).all())
+    del v, p, acc
+    torch.cuda.empty_cache()
+
+
 # one shape per tiling of the bf16 product on 256 compute units (64 x 64, 64 x 128, 128 x 128, 256 x 128,
 # 256 x 192, 256 x 256, 256 x 256 with a split last round), all with ragged last rows and columns, for the
 # fp32 output too
