@@ -88,8 +88,8 @@ __device__ __forceinline__ void buffer_load_lds16(const void* base, unsigned nby
 
 // One tiling of the kernel: BM x BN output tile, K step BK, WAVES waves in a
 // WM x (WAVES/WM) grid. STAGES 0: the ping-pong loop of 8 waves (two LDS arrays
-// for A tiles, three for B tiles); else a ring of STAGES arrays, each an A tile
-// followed by a B tile, loaded STAGES-1 steps ahead.
+// for A tiles, three for B tiles); 4: a ring of four arrays, each an A tile
+// followed by a B tile, loaded three steps ahead.
 template <int BM_, int BN_, int BK_, int STAGES_, int WAVES_, int WM_>
 struct Tiling {
   static constexpr int BM = BM_, BN = BN_, BK = BK_, STAGES = STAGES_, WAVES = WAVES_, WM = WM_;
@@ -108,7 +108,7 @@ struct Tiling {
   static_assert(LOADS * WAVES == SEG_A + SEG_B && SEG_A % WAVES == 0, "stage load must split evenly over waves");
   static_assert(RB * 32 == TM && NI * 16 == TN, "wave tile");
   static_assert(!PING || (WAVES == 8 && BM <= 256 && BN <= 256), "ping-pong: two halves of four waves");
-  static_assert(PING || (STAGES >= 2 && STAGES <= 4 && LOADS * (STAGES - 2) <= 63), "ring, vmcnt range");
+  static_assert(PING || (STAGES == 4 && LOADS * (STAGES - 2) <= 63), "ring, vmcnt range");
   static_assert(ARRAYS * ARRAY * 2 <= 160 * 1024, "LDS");
   // 16-byte chunk c of tile row r sits at slot c ^ swz(r): any 16 consecutive
   // rows read at one chunk (one fragment read, 256 bytes per 16 lanes) land
@@ -373,14 +373,10 @@ __device__ __forceinline__ void row_gemm_tile(const RowGemm& g, int tm, int tn, 
       if (++k == nk) break;
       step(Int<1>{}, k);
       if (++k == nk) break;
-      if constexpr (RING > 2) {
-        step(Int<2>{}, k);
-        if (++k == nk) break;
-      }
-      if constexpr (RING > 3) {
-        step(Int<3>{}, k);
-        if (++k == nk) break;
-      }
+      step(Int<2>{}, k);
+      if (++k == nk) break;
+      step(Int<3>{}, k);
+      if (++k == nk) break;
     }
   }
   __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));  // the repeated loads, before the epilogue takes the arrays
@@ -588,8 +584,8 @@ template <class TL, int NOUT, int EPI, bool BUF>
 __global__ __launch_bounds__(TL::THREADS) void row_gemm_bf16_kernel(RowGemm g) {
   constexpr bool kSplit = std::is_same<TL, TBig>::value;
   static_assert(!kSplit || TMid::THREADS == TL::THREADS, "halves");
-  __shared__ __attribute__((aligned(16))) bf16 L0[TL::ARRAY], L1[TL::ARRAY], L2[TL::ARRAYS > 2 ? TL::ARRAY : 1],
-      L3[TL::ARRAYS > 3 ? TL::ARRAY : 1], L4[TL::ARRAYS > 4 ? TL::ARRAY : 1];
+  __shared__ __attribute__((aligned(16))) bf16 L0[TL::ARRAY], L1[TL::ARRAY], L2[TL::ARRAY], L3[TL::ARRAY],
+      L4[TL::ARRAYS > 4 ? TL::ARRAY : 1];
   const LdsArrays lds{{L0, L1, L2, L3, L4}};
 
   const int tiles_m = (g.M + TL::BM - 1) / TL::BM;
