@@ -449,9 +449,9 @@ __global__ __launch_bounds__(256) void attention_combine_kernel(const float* __r
 // Small launches: 16 queries of one head per workgroup, whose 8 waves split the
 // cached rows (wave w takes the 32-key blocks w, w+8, ...) and merge their
 // softmaxes in LDS. The main kernel walks all rows of a part in one chain of
-// blocks, 0.85 us each, however few workgroups there are; here the chain is an
-// eighth of it and the grid has 16 times the workgroups, at 16 times the loads
-// per product: launch_attention_bf16 says where the line lies.
+// blocks, 0.57 us each at 128-wide heads and 0.41 at 64, however few workgroups there are;
+// here the chain is an eighth of it and the grid has 16 times the workgroups, at 16 times
+// the loads per product: small_is_faster says where the line lies.
 //
 // Per 32-key block of a wave: S^T = K Q^T by v_mfma_f32_16x16x32_bf16, K rows
 // straight from global memory in the A operand's layout (lane: key l16, channels
@@ -616,10 +616,17 @@ __global__ __launch_bounds__(kSmallWaves * 64) void attention_small_kernel(
 
 // Estimated times (us, MI355X): the main kernel takes 9 and 0.57 per 32-key
 // block of 128-wide heads for each round of its workgroups on the CUs, and 4 to
-// merge key parts, the small one 4.5 and 0.26. Measured, main against
-// small: 500 queries and 1000 rows of 2 heads 27.1 and 12.9, 80 x 500 x 8 heads
-// 15.0 and 8.8, 300 x 1600 x 8 28.6 and 18.1, 400 x 512 x 12 18.6 and 16.4; but 800 x
-// 512 x 12 18.9 and 24.1, 1000 x 4000 x 12 42 and 117.
+// merge key parts, the small one 4.5 and 0.26. At 64-wide heads a block counts half,
+// which holds for the small kernel (3.2 + 0.13 a block measured) and not for the main one
+// (5.2 + 0.41). Measured, main against small, 128-wide: 500 queries and 1000 rows of 2 heads
+// 27.1 and 12.9, 80 x 500 x 8 heads 15.0 and 8.8, 300 x 1600 x 8 28.6 and 18.1, 400 x 512 x 12
+// 18.6 and 16.4; but 800 x 512 x 12 18.9 and 24.1, 1000 x 4000 x 12 42 and 117. 64-wide: 500 x
+// 1000 x 2 18.5 and 7.5, 500 x 2000 x 8 22.8 and 12.6; but 2000 x 2000 x 8 26.3 and 39.1, 1000 x
+// 4000 x 12 30.3 and 54.8. The line lies on the main kernel's side: over 21 sizes of 40 to 4000
+// queries and 77 to 8000 rows, with 2, 4, 8, 12 and 24 heads of either width, the small kernel
+// never ran where it is slower, and the main one ran in 36 of 210 launches where it is 6-65%
+// slower (500 x 1000 x 12 64-wide 18.7 and 12.9: the small kernel's second round, counted
+// whole here, shares the CUs with the first).
 bool small_is_faster(int n_q, int n_kv, int heads, int head_dim, long main_wgs, int parts) {
   const long cus = compute_units(), wgs = (long)((n_q + kSmallQ - 1) / kSmallQ) * heads;
   const double blocks = (double)((n_kv + 31L) / 32) * head_dim / 128;

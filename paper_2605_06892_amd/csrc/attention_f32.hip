@@ -20,7 +20,7 @@
 //                   of ONE query.
 //   softmax         online; the maximum and the sum need one exchange between
 //                   the lanes of one query. exp_neg is as exact as expf for
-//                   the arguments here (x <= 0) in half its instructions.
+//                   x <= 0 and normal results, in half its instructions.
 //   O^T += V^T P^T  step e takes the probabilities as they sit in the score
 //                   registers (key row(e, slot)) and the matching rows of V;
 //                   tile dt's row r is channel r*DT + dt, so a lane reads DT
@@ -66,8 +66,8 @@ struct Mfma<16> {
 };
 
 // exp(x) for x <= 0 (NaN stays NaN): 2^t with t = fl(x log2 e), corrected by
-// the remainder x - t ln 2, which is exact to below an ulp. Results under 2^-149
-// are 0.
+// the remainder x - t ln 2, which is exact to below an ulp. Results under 2^-126,
+// which v_exp_f32 flushes (expf does not), are 0: a key's weight of 1e-38 of the greatest.
 __device__ __forceinline__ float exp_neg(float x) {
   const float c = x < -104.f ? -104.f : x;
   const float t = c * 1.44269504088896341f;

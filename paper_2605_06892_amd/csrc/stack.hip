@@ -113,8 +113,8 @@ __device__ __forceinline__ unsigned long long key_bits(unsigned long long k) {
 // coalesced 16-byte accesses, up to 64 channels at a time, and staged in LDS;
 // then one lane per token and sum adds them in channel order, lanes 0-31 the
 // numerators and 32-63 the denominators. At 17 KB of LDS nine such workgroups
-// fit a CU and 75600 tokens are one round, if three waves' registers fit a SIMD:
-// unbounded, the compiler takes 254 (64 tokens on two waves that way: 22.9 us).
+// fit a CU, 73728 tokens on all, if three waves' registers fit a SIMD: unbounded, the
+// compiler takes 254 (64 tokens on two waves that way: 22.9 us).
 // One thread walking each row in global memory took 132 us at 75600 x 64, this
 // takes 14.5 us (4.0 TB/s).
 constexpr int kL1Tokens = 32, kL1Quads = 16;
