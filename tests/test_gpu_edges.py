@@ -245,9 +245,10 @@ def test_l1_rel_of_the_most_tokens():
 
 
 # one shape per tiling of the bf16 product on 256 compute units (64 x 64, 64 x 128, 128 x 128, 256 x 128,
-# 256 x 192, 256 x 256, 256 x 256 with a split last round), all with ragged last rows and columns, for the
-# fp32 output too
-GEMM_SHAPES = [(65, 68), (1000, 1532), (2000, 1532), (4090, 1532), (8190, 1532), (2590, 5116), (8190, 5116)]
+# 256 x 192, 256 x 256, and 256 x 256 with a split last round whose tiles of the last columns have a ragged
+# second half or one past the columns), all with ragged last rows and columns, for the fp32 output too
+GEMM_SHAPES = [(65, 68), (1000, 1532), (2000, 1532), (4090, 1532), (8190, 1532), (2590, 5116), (8190, 5116),
+               (8190, 4988)]
 
 
 # K steps 1 .. 8: the large tilings' one and two steps without a loop, the ends of the loops unrolled by 4 and 6
