@@ -144,7 +144,9 @@ class HsaStack(ctypes.Structure):
 
 # The short calls are bound by this marshalling (an Euler update of 75600 x 16 is 6.6 us of kernel):
 # plain integers, which ctypes converts itself, and the current stream's handle without its
-# Python object.
+# Python object (through two functions that torch does not document; without them, the object).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_device = getattr(torch._C, "_cuda_getDevice", None)
 
 
 def _ptr(t):
@@ -153,7 +155,9 @@ def _ptr(t):
 
 def _stream(stream):
     if stream is None:
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        if _raw_stream and _device:
+            return _raw_stream(_device())
+        stream = torch.cuda.current_stream()
     return stream.cuda_stream
 
 

@@ -473,3 +473,15 @@ def test_active_set_count_inside_the_calls_own_arrays(inside):
         want[slot] = n // 2
     assert torch.equal(idx[:n // 2], want) and bool((idx[n // 2:] == -7).all())
     assert int(count) == n // 2 and int(array[slot]) == n // 2
+
+
+def test_current_stream_of_the_binding(monkeypatch):
+    """The binding's handle of the current stream is torch's, inside and outside a stream's context."""
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        assert H._stream(None) == torch.cuda.current_stream().cuda_stream == side.cuda_stream
+    assert H._stream(None) == torch.cuda.current_stream().cuda_stream
+    monkeypatch.setattr(H, "_raw_stream", None)
+    assert H._stream(None) == torch.cuda.current_stream().cuda_stream
+    with torch.cuda.stream(side):
+        assert H._stream(None) == side.cuda_stream
