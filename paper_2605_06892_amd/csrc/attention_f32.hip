@@ -3,7 +3,7 @@
 //
 // Both contractions run on the matrix cores in fp32 (v_mfma_f32_32x32x2_f32 or
 // 16x16x4: fp32 products and sums, twice the rate of unpacked FMAs), which
-// bound it: they are busy 67% of a launch of 2499 queries, 4999 rows and 12
+// bound it: they are busy 61% of a launch of 2499 queries, 4999 rows and 12
 // heads of 64, the softmax's VALU work taking most of the rest. One workgroup
 // of 8 waves takes 32 (or 16) queries of one head and its waves split the
 // cached rows (wave w takes the 32-key blocks w, w+8, ...), so that even a
@@ -28,7 +28,7 @@
 //
 // Measured against one wave per (query, head) with FMAs and a serial walk over
 // the keys: 682 queries, 1024 rows, 4 x 64 heads 285 -> 17 us; 2499 queries,
-// 4999 rows, 12 x 64 heads 9083 -> 460 us (84 TFLOP/s); its error against
+// 4999 rows, 12 x 64 heads 9083 -> 449 us (85 TFLOP/s); its error against
 // float64 is 0.6 of the former's.
 #include "common.h"
 

@@ -23,7 +23,7 @@
 // SIMD's two waves issues MFMAs and nothing else, the other reads its next
 // fragments and issues loads. With both waves doing both at once, interleaved
 // by the compiler around one barrier per step, the matrix pipes were busy 71%
-// of the Q/K/V launch at 8190 x 5120; they are now 80-83%. The 32x32x16 MFMA
+// of the Q/K/V launch at 8190 x 5120; they are now 79-83%. The 32x32x16 MFMA
 // then ran at a clock of 1.49 GHz (the card's power limit), 16x16x32 runs at
 // 1.61 GHz: it reads and writes half as many accumulators per product. Together
 // that launch went from 1045 to 884 us (1.23 -> 1.46 PFLOP/s), the output
@@ -33,8 +33,8 @@
 // The small tilings run a ring of four arrays, loaded three steps ahead, with
 // one barrier per step: launches of few rows or columns are bound by the
 // latency of one workgroup's chain of steps, which a smaller tile shortens, and
-// by the CUs left without a workgroup. 400 x 8960 x 1536 products went from 100
-// to 38 us, 1000 x 1536 x 1536 from 20.5 to 9.8 us, and those of a block of 500
+// by the CUs left without a workgroup. 400 x 8960 x 1536 products went from 101
+// to 41 us, 1000 x 1536 x 1536 from 21.9 to 11.1 us, and those of a block of 500
 // rows at d = 256 from 8.5-12 to 5-6 us (kernel alone).
 // Every tile row is a contiguous 128-byte run of a token row, so the indexed
 // loads stay coalesced; rows outside the problem are read from a valid row and
