@@ -83,6 +83,25 @@ def test_attention_f32_infinite_value_in_the_last_row(n_kv, dh):
     assert float((got[:, finite] - want[finite]).abs().max()) < 2.0 ** -24 * (16 + n_kv)
 
 
+# 16 and, with 16 heads, 32 queries a workgroup
+@pytest.mark.parametrize("n_q,heads,dh", [(20, 2, 64), (20, 2, 128), (300, 16, 64), (300, 16, 128)])
+def test_attention_f32_four_byte_alignment(n_q, heads, dh):
+    """fp32 arrays need no more than 4-byte alignment: arrays that start one float into a row give the same bits."""
+    g = _gen(n_q + dh)
+    d, n_kv = heads * dh, 77
+    q, k, v = (torch.randn(n, d, generator=g).to(DEV) for n in (n_q, n_kv, n_kv))
+    want = torch.empty(n_q, d, device=DEV)
+    H.hsa_attention_core(q, k, v, n_q, heads, dh, dh ** -0.5, want)
+    shifted = [torch.empty(t.numel() + 1, device=DEV)[1:].view(t.shape) for t in (q, k, v)]
+    for a, b in zip(shifted, (q, k, v)):
+        a.copy_(b)
+    whole = torch.full((n_q * d + 2,), 7.0, device=DEV)
+    out = whole[1:-1].view(n_q, d)
+    H.hsa_attention_core(*shifted, n_q, heads, dh, dh ** -0.5, out)
+    assert torch.equal(out, want)
+    assert float(whole[0]) == 7.0 and float(whole[-1]) == 7.0
+
+
 @pytest.mark.parametrize("dh", [64, 128])
 @pytest.mark.parametrize("size", [1e2, 1e4, 3e4, 1e6])
 def test_attention_f32_large_scores(size, dh):
@@ -226,6 +245,19 @@ def test_l1_rel_edges(n, channels):
     tp.zero_()
     H.hsa_l1_rel_accumulate(tv, tp, ta, True)
     assert torch.count_nonzero(ta) == 0 and torch.equal(tp, tv)
+
+
+@pytest.mark.parametrize("shift", [(1, 0), (0, 1)])
+def test_l1_rel_off_the_16_byte_alignment(shift):
+    """Either array off the 16-byte alignment takes the scalar kernel: the same bits as the vector kernel's."""
+    g = _gen(7)
+    n, c = 100, 64
+    v, p = torch.randn(n, c, generator=g).to(DEV), torch.randn(n, c, generator=g).to(DEV)
+    tv, tp = (torch.empty(n * c + 1, device=DEV)[o:o + n * c].view(n, c).copy_(t) for t, o in zip((v, p), shift))
+    acc, tacc = torch.zeros(n, dtype=torch.float64, device=DEV), torch.zeros(n, dtype=torch.float64, device=DEV)
+    H.hsa_l1_rel_accumulate(v, p, acc, False)
+    H.hsa_l1_rel_accumulate(tv, tp, tacc, False)
+    assert torch.equal(acc, tacc) and torch.equal(tp, v)
 
 
 def test_l1_rel_of_the_most_tokens():
