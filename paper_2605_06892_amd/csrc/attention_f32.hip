@@ -29,7 +29,10 @@
 // Measured against one wave per (query, head) with FMAs and a serial walk over
 // the keys: 682 queries, 1024 rows, 4 x 64 heads 285 -> 17 us; 2499 queries,
 // 4999 rows, 12 x 64 heads 9083 -> 449 us (85 TFLOP/s); its error against
-// float64 is 0.6 of the former's.
+// float64 is 0.6 of the former's. Up to 4 rows of 64-wide heads and 8 of 128-wide
+// it is the slower one (1 query, 1 row 4.1 against 3.0 us, 16 x 8 x 12 heads of 128
+// 6.2 against 5.5): the launch, the trip through LDS and the merge; a single wave for such
+// rows takes 3.8 and 6.3.
 #include "common.h"
 
 namespace hsa {
